@@ -409,6 +409,8 @@ int lbm_init(lbm_ctx **out, const lbm_params *p, void *pop_a, void *pop_b, void 
     }
     c->block_y = 256 / c->block_x;
     c->launch_flags = 0;
+    c->sweep = SweepPlan{0, 0, 0};
+    if (!masked && !grayed && !c->k64.forced) c->sweep = plan_sweep(p->lattice, p->storage, c->grid);
     hipError_t e = hipSuccess;
     if (masked) e = launch_links(p->lattice, c->grid, (const uint8_t *)mask, c->links, c->stream);
     if (grayed) e = hipMemcpyAsync(c->gray, mask, (size_t)pr.n * 4, hipMemcpyDeviceToDevice, c->stream);
@@ -442,6 +444,15 @@ int lbm_step(lbm_ctx *c, int64_t nsteps)
     if (!c) return fail(LBM_ERR_ARG, "ctx is NULL");
     if (nsteps < 0) return fail(LBM_ERR_ARG, "nsteps must be >= 0");
     for (int64_t s = 0; s < nsteps; ++s) {
+        if (c->sweep.tx && nsteps - s >= 2) {  // two steps in one pass
+            const hipError_t e = launch_sweep(c->p.lattice, c->p.storage, c->p.order, c->grid, c->k64, c->k32, c->sweep,
+                                              c->pop[c->cur], c->pop[c->cur ^ 1], c->stream);
+            if (e != hipSuccess) return fail_hip(e, "two-step kernel launch");
+            c->cur ^= 1;
+            c->t += 2;
+            ++s;
+            continue;
+        }
         hipError_t e = launch_step(c->p.lattice, c->p.storage, c->p.order, c->grid, c->k64, c->k32, c->links,
                                    c->gray, c->pop[c->cur], c->pop[c->cur ^ 1], c->block_x, c->block_y,
                                    c->launch_flags, c->stream);
@@ -527,6 +538,7 @@ int lbm_set_launch(lbm_ctx *c, int32_t block_x, int32_t block_y, int32_t flags)
     c->block_x = block_x;
     c->block_y = block_y;
     c->launch_flags = flags;
+    c->sweep = SweepPlan{0, 0, 0};  // the launch asked for is a single step's
     return LBM_OK;
 }
 

@@ -80,6 +80,17 @@ hipError_t launch_step(int lattice, int storage, int order, const Grid &g, const
                        const StepConsts<float> &k32, const uint32_t *links, const float *gray, const void *src,
                        void *dst, int block_x, int block_y, int flags, hipStream_t stream);
 
+// ---- two steps in one pass (sweep.hip) ----
+// How a sweep over a grid is cut: tiles of tx columns by ty rows, each column of tiles in `segs`
+// runs of z-planes; tx = 0 where two single steps are the faster way.
+struct SweepPlan {
+    int tx, ty, segs;
+};
+SweepPlan plan_sweep(int lattice, int storage, const Grid &g);
+hipError_t launch_sweep(int lattice, int storage, int order, const Grid &g, const StepConsts<double> &k64,
+                        const StepConsts<float> &k32, const SweepPlan &p, const void *src, void *dst,
+                        hipStream_t stream);
+
 // ---- the gradient path (reverse sweep) ----
 constexpr int kGradPartialsHost = 7;  // per work-group: dJ/dK (6, symmetric part: xx yy zz xy xz yz), dJ/dtau
 // lam: adjoint populations (q N elements, the population layout of Grid) in the arithmetic

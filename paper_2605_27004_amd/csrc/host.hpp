@@ -81,6 +81,7 @@ struct lbm_ctx {
     int64_t t;
     int block_x, block_y;
     int launch_flags;
+    lbm::SweepPlan sweep;    // how lbm_step takes steps two at a time (tx = 0: it does not)
 };
 
 namespace lbm {

@@ -1,0 +1,331 @@
+// sweep.hip -- two steps of the periodic update in one pass over HBM (D3Q19 and D3Q27, FP32 and
+// FP64 storage, no walls, gray cells or body force).
+//
+// A single step reads and writes every population once, which is what bounds it (2 q sizeof(S)
+// bytes per cell and step). A sweep reads and writes them once per TWO steps: a work-group owns a
+// tile of columns in x and y and walks up in z. On each plane it makes the first step on the tile
+// and one cell around it (from the state in HBM, by the pull of k_step), passes the post-collision
+// values to its neighbours through LDS, and makes the second step one plane below, which it stores.
+// The arithmetic is collide_cell on the same values in the same order, rounded to the storage type
+// in between, so the result is bit for bit that of two single steps.
+//
+// What bounds it: the first step is made again on the tile's rim (11 rows of lanes for 8 rows of
+// cells at the D3Q19 256^3 tile below), so FP32 is bound by its VALU work (596 instructions per
+// two steps and cell, VALU 78% busy, the clock down to 1.7 GHz) and FP64 by HBM and LDS space (one
+// work-group of 10 waves per compute unit). Us per step, two single steps -> sweep:
+//   D3Q19 FP32 256^3 389.6 -> 262.5, 128^3 52.1 -> 38.4; FP64 256^3 808.9 -> 505.0,
+//   250 x 190 x 130 404.6 -> 216.4; D3Q27 FP32 256^3 564.8 -> 447.4, FP64 256^3 1191 -> 904.
+//
+//  * Lanes: wave w of the tile is one row of 64 cells (two of 32), so the stores of a wave are
+//    whole cache lines, and the columns left and right of the tile sit in the last waves. One flat
+//    lane order over the rim-included rows split each stored row between two waves: 1.28 x the
+//    bytes written and 346 instead of 288 us.
+//  * The next plane's pulls are issued before the first collision and waited for after the second
+//    one, so a plane's whole arithmetic covers them.
+//  * Every work-group of a segment walks z in step with its neighbours, whose pulls share its rim
+//    lines in the XCD's L2 (consecutive tiles on one XCD): FETCH_SIZE 1.15 x one read of the state
+//    against 2.1 x, and 275 against 385 us, when each work-group took an equal run of planes that
+//    starts anywhere.
+#include <algorithm>
+
+#include <hip/hip_runtime.h>
+
+#include "cell.hpp"
+#include "common.hpp"
+
+#pragma clang fp contract(off)
+
+namespace lbm {
+namespace {
+
+using namespace cell;
+
+// Place in LDS of direction i among the directions with the same c_z; -1 for those that stay in
+// their column (c_x = c_y = 0: rest, +z, -z), which their lane keeps.
+template <int LAT> struct Ring {
+    int slot[Lattice<LAT>::Q];
+    int count[3];  // by c_z + 1
+    constexpr Ring() : slot(), count()
+    {
+        for (int i = 0; i < Lattice<LAT>::Q; ++i) {
+            const PairRow v = i == 0 ? PairRow{0, 0, 0} : Lattice<LAT>::pair((i - 1) / 2);
+            slot[i] = (v.cx == 0 && v.cy == 0) ? -1 : count[((i & 1) ? v.cz : -v.cz) + 1]++;
+        }
+    }
+};
+
+constexpr int cz_of(PairRow v, int i) { return (i & 1) ? v.cz : -v.cz; }
+
+// Raw buffer resource on a z-plane (the same for the whole work-group, see plane_stores): the q
+// pulls of a cell then take nine lane offsets and a scalar offset per direction, with no address
+// arithmetic per load.
+template <typename S> __device__ inline __amdgpu_buffer_rsrc_t plane_rsrc(const S *p)
+{
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    const uint64_t u = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32)) << 32) |
+                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<S *>(u), (short)0, -1, 0x00020000);
+}
+
+template <typename S> __device__ inline S ld_buf(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t soff)
+{
+    if constexpr (sizeof(S) == 4)
+        return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, (int)soff, 0));
+    else
+        return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, (int)soff, 0));
+}
+
+// v[0] goes to the end, the others move down.
+template <typename P, int N> __device__ inline void rotate(P *(&v)[N])
+{
+    P *f = v[0];
+#pragma unroll
+    for (int j = 0; j + 1 < N; ++j) v[j] = v[j + 1];
+    v[N - 1] = f;
+}
+
+// Barrier that orders LDS only: the work-group's global loads and stores stay in flight across it.
+__device__ inline void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Two steps over the tile (tx, ty) of TX columns by ty_cells rows (at most TYM) and the z-planes of
+// one of `segs` segments. The second step of plane z needs the first step's values of planes z - 1
+// (c_z = +1), z (c_z = 0) and z + 1 (c_z = -1). REGS: each lane reads its neighbours' values as
+// soon as a plane is there and keeps them in registers until their turn, so LDS holds one plane,
+// twice (one barrier per plane); else LDS holds the planes until their turn (three, two and one of
+// them, two barriers per plane), for FP64, whose registers would spill (505 against 570 us at
+// D3Q19 256^3; FP32 the other way round, 265 against 285 us).
+template <int LAT, typename S, int ORDER, int TX, int TYM, bool REGS>
+__global__ __launch_bounds__(((TX + 2) * (TYM + 2) + 63) / 64 * 64) void k_sweep(
+    const S *__restrict__ src, S *__restrict__ dst, const Grid g, const StepConsts<typename Conv<S>::C> k,
+    const int ty_cells, const uint32_t tiles_x, const uint32_t tiles, const uint32_t segs)
+{
+    using L = Lattice<LAT>;
+    using C = typename Conv<S>::C;
+    constexpr int NP = L::NP, W = TX + 2, COLS = W * (TYM + 2);
+    constexpr Ring<LAT> R{};
+    constexpr PullOrder<LAT> kPull{};
+    constexpr int NU = REGS ? 2 : 3, NF = 2, ND = REGS ? 2 : 1;  // planes of c_z = +1, 0, -1 values in LDS
+    __shared__ S lds[(NU * R.count[2] + NF * R.count[1] + ND * R.count[0]) * COLS];
+
+    // lanes 0 .. TX H - 1: the tile's own x, row by row; then the columns left and right of it
+    const int H = ty_cells + 2, IN = TX * H;
+    const int t = threadIdx.x;
+    const bool column = t < W * H;
+    int hx, hy;
+    if (t < IN) {
+        hx = 1 + t % TX;
+        hy = t / TX;
+    } else {
+        const int h = column ? t - IN : 0;
+        hx = (h & 1) ? W - 1 : 0;
+        hy = h >> 1;
+    }
+    // LDS places of this column, [0] the plane read, the last one the plane written
+    S *up[NU], *flat[NF], *down[ND];
+    {
+        S *p = lds + hy * W + hx;
+#pragma unroll
+        for (int j = 0; j < NU; ++j, p += R.count[2] * COLS) up[j] = p;
+#pragma unroll
+        for (int j = 0; j < NF; ++j, p += R.count[1] * COLS) flat[j] = p;
+#pragma unroll
+        for (int j = 0; j < ND; ++j, p += R.count[0] * COLS) down[j] = p;
+    }
+    const uint32_t step = g.bc * (uint32_t)sizeof(S);
+
+    // consecutive tiles of a segment on one XCD
+    const uint32_t n8 = gridDim.x / 8u, r8 = gridDim.x % 8u, xcd = blockIdx.x % 8u, loc = blockIdx.x / 8u;
+    const uint32_t b = xcd < r8 ? xcd * (n8 + 1u) + loc : r8 * (n8 + 1u) + (xcd - r8) * n8 + loc;
+    const uint32_t tile = b % tiles, seg = b / tiles;
+    const int z_begin = (int)((uint64_t)g.nz * seg / segs), z_end = (int)((uint64_t)g.nz * (seg + 1u) / segs);
+    const int xo = (int)(tile % tiles_x) * TX + hx - 1, yo = (int)(tile / tiles_x) * ty_cells + hy - 1;
+    const bool inner = t < IN && hy >= 1 && hy <= ty_cells && xo < g.nx && yo < g.ny;
+    int z = z_begin == 0 ? g.nz - 1 : z_begin - 1;
+    const Cell c = cell_of(g, (xo + g.nx) % g.nx, (yo + g.ny) % g.ny, z);
+    // in-plane byte offsets of the nine columns a pull reads
+    uint32_t off[3][3];
+#pragma unroll
+    for (int cy = -1; cy <= 1; ++cy)
+#pragma unroll
+        for (int cx = -1; cx <= 1; ++cx)
+            off[cy + 1][cx + 1] = (c.at + back(c.ox, cx) + back(c.oy, cy)) * (uint32_t)sizeof(S);
+
+    S pre[L::Q];
+    auto load = [&](int zz) {
+        const __amdgpu_buffer_rsrc_t r0 = plane_rsrc(src + (uint64_t)zz * g.zs);
+        const __amdgpu_buffer_rsrc_t rm = plane_rsrc(src + (uint64_t)(zz == 0 ? g.nz - 1 : zz - 1) * g.zs);
+        const __amdgpu_buffer_rsrc_t rp = plane_rsrc(src + (uint64_t)(zz == g.nz - 1 ? 0 : zz + 1) * g.zs);
+#pragma unroll
+        for (int j = 0; j < L::Q; ++j) {
+            const int i = kPull.dir[j];
+            const PairRow v = i == 0 ? PairRow{0, 0, 0} : L::pair((i - 1) / 2);
+            const int sg = (i & 1) ? 1 : -1, cz = sg * v.cz;
+            pre[i] = ld_buf<S>(cz > 0 ? rm : (cz < 0 ? rp : r0), off[sg * v.cy + 1][sg * v.cx + 1],
+                               (uint32_t)i * step);
+        }
+    };
+    load(z);
+
+    // values waiting for their plane's second step: w1 one plane old (c_z = 0 and +1), w2 two (+1)
+    C w1[L::Q], w2[L::Q];
+#pragma unroll
+    for (int i = 0; i < L::Q; ++i) w1[i] = w2[i] = C(0);
+    const int count = z_end - z_begin + 2;
+    for (int it = 0; it < count; ++it) {
+        C gp[NP + 1], gm[NP + 1];
+        gp[0] = Conv<S>::ld(pre[0]);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            gp[p + 1] = Conv<S>::ld(pre[2 * p + 1]);
+            gm[p + 1] = Conv<S>::ld(pre[2 * p + 2]);
+        }
+        const int below = z == 0 ? g.nz - 1 : z - 1;  // the plane the second step writes
+        z = z == g.nz - 1 ? 0 : z + 1;
+        if (it + 1 < count) load(z);
+        __builtin_amdgcn_sched_barrier(0);
+        collide_cell<LAT, ORDER, false, C, kClose<S>>(k, gp, gm);
+        C now[L::Q];
+#pragma unroll
+        for (int i = 0; i < L::Q; ++i) {
+            const S val = Conv<S>::st(i == 0 ? gp[0] : ((i & 1) ? gp[(i - 1) / 2 + 1] : gm[(i - 1) / 2 + 1]));
+            const int cz = i == 0 ? 0 : cz_of(L::pair((i - 1) / 2), i);
+            if (R.slot[i] < 0)
+                now[i] = Conv<S>::ld(val);
+            else if (column)
+                (cz > 0 ? up[NU - 1] : (cz == 0 ? flat[NF - 1] : down[ND - 1]))[R.slot[i] * COLS] = val;
+        }
+        lds_barrier();
+        if (inner) {
+            constexpr int RU = REGS ? NU - 1 : 0, RF = REGS ? NF - 1 : 0, RD = ND - 1;
+#pragma unroll
+            for (int i = 0; i < L::Q; ++i) {
+                const PairRow v = i == 0 ? PairRow{0, 0, 0} : L::pair((i - 1) / 2);
+                const int sg = (i & 1) ? 1 : -1, cz = sg * v.cz;
+                if (R.slot[i] >= 0)
+                    now[i] = Conv<S>::ld((cz > 0 ? up[RU] : (cz == 0 ? flat[RF] : down[RD]))
+                                             [R.slot[i] * COLS - sg * v.cx - sg * v.cy * W]);
+            }
+#pragma unroll
+            for (int i = 0; i < L::Q; ++i) {
+                const int cz = i == 0 ? 0 : cz_of(L::pair((i - 1) / 2), i);
+                const bool wait = REGS || R.slot[i] < 0;
+                const C val = !wait || cz < 0 ? now[i] : (cz == 0 ? w1[i] : w2[i]);
+                if (wait && cz > 0) w2[i] = w1[i];
+                if (wait && cz >= 0) w1[i] = now[i];
+                if (i == 0) gp[0] = val;
+                else if (i & 1) gp[(i - 1) / 2 + 1] = val;
+                else gm[(i - 1) / 2 + 1] = val;
+            }
+            collide_cell<LAT, ORDER, false, C, kClose<S>>(k, gp, gm);
+        }
+        // the next plane's loads end here, before this plane's stores are issued
+#pragma unroll
+        for (int i = 0; i < L::Q; ++i) asm volatile("" : "+v"(pre[i]));
+        if (it >= 2 && inner) {
+            const PlaneStores ps = plane_stores(dst, g, Ref{(uint64_t)below * g.zs, c.at});
+            st_plane(ps, 0, Conv<S>::st(gp[0]));
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                st_plane(ps, 2 * p + 1, Conv<S>::st(gp[p + 1]));
+                st_plane(ps, 2 * p + 2, Conv<S>::st(gm[p + 1]));
+            }
+        }
+        if (!REGS) lds_barrier();
+        rotate(up);
+        rotate(flat);
+        rotate(down);
+    }
+}
+
+}  // namespace
+
+namespace {
+
+constexpr uint32_t kCus = 256;  // compute units of the MI355X; one work-group of a sweep runs on each
+
+// Tile widths and largest heights of the compiled sweeps (the LDS of a tile and its rim, and 1,024
+// lanes), and the measured time of one row of `tx` cells of one plane (us); a plane of a tile of h
+// rows takes the time of h + 1.
+struct SweepTile {
+    int lattice, storage, tx, tym;
+    double row_us;
+};
+constexpr SweepTile kTiles[] = {
+    {kD3Q19, kF32, 64, 13, 0.46},
+    {kD3Q19, kF64, 32, 16, 0.46},
+    {kD3Q19, kF64, 64, 7, 0.87},
+    {kD3Q27, kF32, 64, 9, 0.78},
+    {kD3Q27, kF64, 32, 10, 0.72},
+};
+
+}  // namespace
+
+// The cut of a grid into tiles and segments, from the time that a cut takes: rounds of one
+// work-group per compute unit x planes (two more than the segment's, for the rim) x rows. Measured
+// over grids of 30 x 25 x 40 to 256^3, even and odd, it is right to 5% for D3Q19 and 10% for D3Q27.
+// Against it stands the time of two single steps: 2 us a launch and the bytes at 6.3 TB/s, or 4.7
+// TB/s where rows are no whole cache lines (their stores then leave partial ones). The line so lies
+// near 80^3: below, the work-groups are too few and their rims too large (us per step, single against
+// sweep, D3Q19 FP32: 48^3 6.0 / 6.2, 64^3 8.05 / 7.8, 77 x 85 x 60 15.8 / 16.0, 96^3 25.2 / 22.3,
+// 150 x 101 x 75 34.9 / 30.3; D3Q27 FP32: 96^3 35.5 / 36.1, 128^3 73.8 / 66.8).
+SweepPlan plan_sweep(int lattice, int storage, const Grid &g)
+{
+    SweepPlan best{0, 0, 0};
+    const int bytes = storage == kF64 ? 8 : 4;
+    const double q = lattice == kD3Q19 ? 19.0 : 27.0;
+    const double rate = g.nx * bytes % 128 == 0 ? 6.3e6 : 4.7e6;  // bytes per us
+    double best_us = 2.0 * (2.0 + 2.0 * q * bytes * g.n / rate) / 1.05;
+    for (const SweepTile &t : kTiles) {
+        if (t.lattice != lattice || t.storage != storage) continue;
+        // D3Q19 FP64: rows of 32 cells where they are whole cache lines (256^3: 505 against 532 us),
+        // else of 64 cells, which leave half the partial lines (250 x 190 x 130: 249 against 214 us)
+        if (lattice == kD3Q19 && storage == kF64 && (t.tx == 32) != (g.nx % 16 == 0)) continue;
+        const int64_t tx = (g.nx + t.tx - 1) / t.tx;
+        for (int ty = t.tym; ty >= 3; --ty) {
+            const int64_t tiles = tx * ((g.ny + ty - 1) / ty);
+            for (int segs = 1; segs <= std::max(1, g.nz / 2) && segs <= 64; ++segs) {
+                const int64_t rounds = (tiles * segs + kCus - 1) / kCus;
+                const double us = 2.0 + (double)rounds * ((g.nz + segs - 1) / segs + 2) * (ty + 1) * t.row_us;
+                if (us < best_us) {
+                    best_us = us;
+                    best = SweepPlan{t.tx, ty, segs};
+                }
+            }
+        }
+    }
+    return best;
+}
+
+hipError_t launch_sweep(int lattice, int storage, int order, const Grid &g, const StepConsts<double> &k64,
+                        const StepConsts<float> &k32, const SweepPlan &p, const void *src, void *dst,
+                        hipStream_t stream)
+{
+    const uint32_t tiles_x = (uint32_t)((g.nx + p.tx - 1) / p.tx), tiles_y = (uint32_t)((g.ny + p.ty - 1) / p.ty);
+    const uint32_t tiles = tiles_x * tiles_y;
+    const dim3 grid(tiles * (uint32_t)p.segs);
+    const dim3 block((uint32_t)((p.tx + 2) * (p.ty + 2) + 63) / 64 * 64);
+#define LBM_SWEEP(LAT, S, TX, TYM, REGS, KC)                                                                       \
+    do {                                                                                                         \
+        if (order == 2)                                                                                          \
+            hipLaunchKernelGGL((k_sweep<LAT, S, 2, TX, TYM, REGS>), grid, block, 0, stream, (const S *)src,        \
+                               (S *)dst, g, KC, p.ty, tiles_x, tiles, (uint32_t)p.segs);                         \
+        else                                                                                                     \
+            hipLaunchKernelGGL((k_sweep<LAT, S, 3, TX, TYM, REGS>), grid, block, 0, stream, (const S *)src,        \
+                               (S *)dst, g, KC, p.ty, tiles_x, tiles, (uint32_t)p.segs);                         \
+        return hipGetLastError();                                                                                \
+    } while (0)
+    if (lattice == kD3Q19 && storage == kF32) LBM_SWEEP(kD3Q19, float, 64, 13, true, k32);
+    if (lattice == kD3Q19 && storage == kF64 && p.tx == 32) LBM_SWEEP(kD3Q19, double, 32, 16, false, k64);
+    if (lattice == kD3Q19 && storage == kF64) LBM_SWEEP(kD3Q19, double, 64, 7, false, k64);
+    if (lattice == kD3Q27 && storage == kF32) LBM_SWEEP(kD3Q27, float, 64, 9, true, k32);
+    if (lattice == kD3Q27 && storage == kF64) LBM_SWEEP(kD3Q27, double, 32, 10, false, k64);
+#undef LBM_SWEEP
+    return hipErrorInvalidValue;
+}
+
+}  // namespace lbm
