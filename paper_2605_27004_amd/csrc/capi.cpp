@@ -307,6 +307,64 @@ template StepConsts<double> consts_for<double>(const lbm_params &, const Prepare
 
 using namespace lbm::host;
 
+namespace {
+
+// Steps the next launch takes when `left` >= 1 are to be taken: a tiled launch's share (the steps
+// spread evenly over the launches), the two of a sweep, or one.
+int64_t pass_steps(const lbm_ctx *c, int64_t left)
+{
+    if (c->tile.shape >= 0) {
+        const int64_t passes = (left + c->tile.steps - 1) / c->tile.steps;
+        return (left + passes - 1) / passes;
+    }
+    return c->sweep.tx && left >= 2 ? 2 : 1;
+}
+
+// One launch of k = pass_steps steps from src to dst.
+hipError_t launch_pass(const lbm_ctx *c, int64_t k, const void *src, void *dst)
+{
+    if (k == 1)
+        return launch_step(c->p.lattice, c->p.storage, c->p.order, c->grid, c->k64, c->k32, c->links, c->gray, src,
+                           dst, c->block_x, c->block_y, c->launch_flags, c->stream);
+    if (c->tile.shape >= 0)
+        return launch_tile(c->p.storage, c->p.order, c->grid, c->k64, c->k32, c->links, c->gray, src, dst, 0, c->tile,
+                           (int)k, c->stream);
+    return launch_sweep(c->p.lattice, c->p.storage, c->p.order, c->grid, c->k64, c->k32, c->sweep, src, dst,
+                        c->stream);
+}
+
+// n >= 1 steps from src to dst through the context's population buffers (src may be neither of them).
+hipError_t advance(const lbm_ctx *c, const void *src, void *dst, int64_t n)
+{
+    for (int i = 0; n > 0; i ^= 1) {
+        const int64_t k = pass_steps(c, n);
+        void *out = k == n ? dst : c->pop[i];
+        const hipError_t e = launch_pass(c, k, src, out);
+        if (e != hipSuccess) return e;
+        src = out;
+        n -= k;
+    }
+    return hipSuccess;
+}
+
+// n >= 0 steps from src, each state kept: state s (after s + 1 steps) at base + s stride bytes.
+hipError_t record(const lbm_ctx *c, const void *src, char *base, int64_t stride, int64_t n)
+{
+    while (n > 0) {
+        const int64_t k = c->tile.shape >= 0 ? pass_steps(c, n) : 1;
+        const hipError_t e = k == 1 ? launch_pass(c, 1, src, base)
+                                    : launch_tile(c->p.storage, c->p.order, c->grid, c->k64, c->k32, c->links, c->gray,
+                                                  src, base, (uint64_t)(stride / c->pr.bytes), c->tile, (int)k, c->stream);
+        if (e != hipSuccess) return e;
+        base += stride * k;
+        src = base - stride;
+        n -= k;
+    }
+    return hipSuccess;
+}
+
+}  // namespace
+
 extern "C" {
 
 int lbm_lattice_info(int32_t lattice, int32_t *q, int32_t *d, int32_t *c, double *w, int32_t *opp)
@@ -410,7 +468,14 @@ int lbm_init(lbm_ctx **out, const lbm_params *p, void *pop_a, void *pop_b, void 
     c->block_y = 256 / c->block_x;
     c->launch_flags = 0;
     c->sweep = SweepPlan{0, 0, 0};
-    if (!masked && !grayed && !c->k64.forced) c->sweep = plan_sweep(p->lattice, p->storage, c->grid);
+    c->tile = TilePlan{-1, 1};
+    const bool general = masked || grayed || c->k64.forced;
+    if (p->lattice == LBM_D2Q9) {
+        if (tile_serves(p->storage, grayed, masked || c->k64.forced))
+            c->tile = plan_tile(p->storage, c->grid, general);
+    } else if (!general) {
+        c->sweep = plan_sweep(p->lattice, p->storage, c->grid);
+    }
     hipError_t e = hipSuccess;
     if (masked) e = launch_links(p->lattice, c->grid, (const uint8_t *)mask, c->links, c->stream);
     if (grayed) e = hipMemcpyAsync(c->gray, mask, (size_t)pr.n * 4, hipMemcpyDeviceToDevice, c->stream);
@@ -443,22 +508,13 @@ int lbm_step(lbm_ctx *c, int64_t nsteps)
 {
     if (!c) return fail(LBM_ERR_ARG, "ctx is NULL");
     if (nsteps < 0) return fail(LBM_ERR_ARG, "nsteps must be >= 0");
-    for (int64_t s = 0; s < nsteps; ++s) {
-        if (c->sweep.tx && nsteps - s >= 2) {  // two steps in one pass
-            const hipError_t e = launch_sweep(c->p.lattice, c->p.storage, c->p.order, c->grid, c->k64, c->k32, c->sweep,
-                                              c->pop[c->cur], c->pop[c->cur ^ 1], c->stream);
-            if (e != hipSuccess) return fail_hip(e, "two-step kernel launch");
-            c->cur ^= 1;
-            c->t += 2;
-            ++s;
-            continue;
-        }
-        hipError_t e = launch_step(c->p.lattice, c->p.storage, c->p.order, c->grid, c->k64, c->k32, c->links,
-                                   c->gray, c->pop[c->cur], c->pop[c->cur ^ 1], c->block_x, c->block_y,
-                                   c->launch_flags, c->stream);
+    while (nsteps > 0) {
+        const int64_t k = pass_steps(c, nsteps);
+        const hipError_t e = launch_pass(c, k, c->pop[c->cur], c->pop[c->cur ^ 1]);
         if (e != hipSuccess) return fail_hip(e, "step kernel launch");
         c->cur ^= 1;
-        ++c->t;
+        c->t += k;
+        nsteps -= k;
     }
     return LBM_OK;
 }
@@ -539,6 +595,7 @@ int lbm_set_launch(lbm_ctx *c, int32_t block_x, int32_t block_y, int32_t flags)
     c->block_y = block_y;
     c->launch_flags = flags;
     c->sweep = SweepPlan{0, 0, 0};  // the launch asked for is a single step's
+    c->tile = TilePlan{-1, 1};
     return LBM_OK;
 }
 
@@ -614,26 +671,19 @@ int lbm_grad(lbm_ctx *c, const lbm_grad_spec *spec, void *workspace, double *obj
     auto ckpt = [&](int64_t s) { return (void *)(ws + l.ckpt + s * pstride); };
     auto segst = [&](int64_t t) { return (void *)(ws + l.seg + (t - 1) * pstride); };  // t >= 1
 
-    // forward pass. Each step runs from one buffer into another, as in lbm_step, but the step
-    // that ends a segment writes straight into the next segment's checkpoint, and the steps of
-    // the last segment write straight into the segment buffer, from which the reverse sweep then
-    // takes that segment without recomputing it (the step is deterministic, so these are bitwise
-    // the states a recompute gives). Only the initial state is copied.
+    // forward pass, as lbm_step takes the steps: every segment ends straight in the next one's
+    // checkpoint, and the states of the last segment go into the segment buffer, from which the
+    // reverse sweep then takes that segment without recomputing it (the step is deterministic, so
+    // these are bitwise the states a recompute gives). Only the initial state is copied.
     if (l.nseg > 0) {
         e = hipMemcpyAsync(ckpt(0), c->pop[c->cur], popb, hipMemcpyDeviceToDevice, st);
         if (e != hipSuccess) return fail_hip(e, "checkpoint copy");
-        const void *src = ckpt(0);
-        for (int64_t sgi = 0; sgi < l.nseg; ++sgi) {
-            const int64_t len = std::min(spec->checkpoint_every, spec->nsteps - sgi * spec->checkpoint_every);
-            const bool last = sgi == l.nseg - 1;
-            for (int64_t t = 1; t <= len; ++t) {
-                void *dst = t == len ? (last ? c->pop[0] : ckpt(sgi + 1)) : (last ? segst(t) : c->pop[t & 1]);
-                e = launch_step(c->p.lattice, c->p.storage, c->p.order, c->grid, c->k64, c->k32, c->links, c->gray,
-                                src, dst, c->block_x, c->block_y, c->launch_flags, st);
-                if (e != hipSuccess) return fail_hip(e, "forward step");
-                src = dst;
-            }
-        }
+        for (int64_t sgi = 0; sgi + 1 < l.nseg && e == hipSuccess; ++sgi)
+            e = advance(c, ckpt(sgi), ckpt(sgi + 1), spec->checkpoint_every);
+        const int64_t len = spec->nsteps - (l.nseg - 1) * spec->checkpoint_every;
+        if (e == hipSuccess) e = record(c, ckpt(l.nseg - 1), (char *)segst(1), pstride, len - 1);
+        if (e == hipSuccess) e = launch_pass(c, 1, len > 1 ? segst(len - 1) : ckpt(l.nseg - 1), c->pop[0]);
+        if (e != hipSuccess) return fail_hip(e, "forward step");
         c->cur = 0;
         c->t += spec->nsteps;
     }
@@ -651,11 +701,8 @@ int lbm_grad(lbm_ctx *c, const lbm_grad_spec *spec, void *workspace, double *obj
         const int64_t len = std::min(spec->checkpoint_every, spec->nsteps - sgi * spec->checkpoint_every);
         auto state = [&](int64_t t) { return t == 0 ? ckpt(sgi) : segst(t); };
         // the last segment's states are already there from the forward pass
-        for (int64_t t = 1; t < len && sgi < l.nseg - 1; ++t) {
-            e = launch_step(c->p.lattice, c->p.storage, c->p.order, c->grid, c->k64, c->k32, c->links, c->gray,
-                            state(t - 1), state(t), c->block_x, c->block_y, c->launch_flags, st);
-            if (e != hipSuccess) return fail_hip(e, "segment recompute");
-        }
+        if (sgi < l.nseg - 1) e = record(c, ckpt(sgi), (char *)segst(1), pstride, len - 1);
+        if (e != hipSuccess) return fail_hip(e, "segment recompute");
         for (int64_t t = len - 1; t >= 0; --t) {
             e = launch_adjoint(c->p.lattice, c->p.storage, c->p.order, c->grid, c->k64, c->k32, state(t), lam_in,
                                lam_out, c->gray, c->links, dmask, gpart, st);

@@ -81,7 +81,8 @@ struct lbm_ctx {
     int64_t t;
     int block_x, block_y;
     int launch_flags;
-    lbm::SweepPlan sweep;    // how lbm_step takes steps two at a time (tx = 0: it does not)
+    lbm::SweepPlan sweep;    // how steps are taken two at a time (tx = 0: they are not)
+    lbm::TilePlan tile;      // how several steps of a D2Q9 grid go into one launch (shape -1: none do)
 };
 
 namespace lbm {
