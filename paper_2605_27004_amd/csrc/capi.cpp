@@ -466,7 +466,7 @@ int lbm_init(lbm_ctx **out, const lbm_params *p, void *pop_a, void *pop_b, void 
         }
     }
     c->block_y = 256 / c->block_x;
-    c->launch_flags = 0;
+    c->launch_flags = kLaunchDefault;
     c->sweep = SweepPlan{0, 0, 0};
     c->tile = TilePlan{-1, 1};
     const bool general = masked || grayed || c->k64.forced;

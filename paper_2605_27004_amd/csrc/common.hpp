@@ -74,6 +74,7 @@ hipError_t launch_init(int lattice, int storage, int order, const Grid &g, const
 constexpr int kLaunchXcdSlabs = 1;     // XCD-contiguous tile order
 constexpr int kLaunchShiftedPull = 2;  // every pull a shifted load (no lane exchange)
 constexpr int kLaunchStreamOnly = 1 << 8;  // library-internal: pulls and stores only (no collision)
+constexpr int kLaunchDefault = 1 << 9;     // library-internal: the caller has not shaped the launch
 
 // gray: per-cell gray fraction m (partial bounce-back) or null.
 hipError_t launch_step(int lattice, int storage, int order, const Grid &g, const StepConsts<double> &k64,

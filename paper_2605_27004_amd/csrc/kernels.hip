@@ -50,24 +50,19 @@ using namespace cell;
 struct TileMap {
     uint32_t tiles_x, tiles_y, nblocks;
     uint32_t xcd_slabs;
-    uint32_t row_xcd;  // the tiles of one row on one XCD (see tile_of)
+    uint32_t group;  // consecutive tiles that share an XCD and follow each other there (see tile_of)
+    uint32_t mx;     // kPullFlat: floor(2^32 / nx) (0xffffffff for nx = 1): cell of a z-plane -> x, y
 };
 
 __device__ inline uint32_t tile_of(const TileMap &m, uint32_t b)
 {
     if (!m.xcd_slabs) {
-        // Work-groups go to the 8 XCDs in turn (b mod 8). With row_xcd, each group of 8 rows of
-        // tiles_x tiles is dispatched so that the tiles of one row share an XCD and follow each
-        // other: block b of the group takes row b mod 8, tile b / 8. The links step reads lines
-        // that the tiles of a row share (shifted and bounce-back pulls), which the XCD's L2 then
-        // serves once: 512^3 porous medium FP16 2,778 -> 2,647 us, FP32 4,854 -> 4,812 us. The
-        // periodic step with shifted pulls got slower with it (D3Q19 512^3: 3,377 -> 3,484 us).
-        const uint32_t tx = m.tiles_x, grp = 8u * tx;
-        if (!m.row_xcd || tx == 1u) return b;
+        if (m.group <= 1u) return b;
+        const uint32_t grp = 8u * m.group;
         const uint32_t full = (m.nblocks / grp) * grp;  // a ragged last group keeps the plain order
         if (b >= full) return b;
         const uint32_t j = b % grp;
-        return (b - j) + (j % 8u) * tx + j / 8u;
+        return (b - j) + (j % 8u) * m.group + j / 8u;
     }
     const uint32_t q = m.nblocks / 8u, r = m.nblocks % 8u;
     const uint32_t xcd = b % 8u, local = b / 8u;
@@ -94,9 +89,11 @@ enum StepMode : int { kPlain = 0, kLinks = 1, kGray = 2, kStream = 3 };
 // edge values would need loads of their own; measured that way, the exchange lost to shifted
 // loads (D3Q19 FP32 512^3: 3.55 vs 3.40 ms per step; 448^3 in 64-wide work-groups: 2.83 vs
 // 2.24 ms), so such launches use the shifted pull.
-// How the step kernel pulls (launch_step picks): every population with its own shifted load, or
-// the lane exchange inside whole rows (pull_aligned, or pull_rows_lds for FP16 storage).
-enum PullKind : int { kPullShifted = 0, kPullRows = 1 };
+// How the step kernel pulls (launch_step picks): every population with its own shifted load, in
+// work-groups that are boxes of block_x x block_y cells (kPullShifted) or runs of 256 consecutive
+// cells of a z-plane (kPullFlat); or the lane exchange inside whole rows (kPullRows: pull_aligned, or
+// pull_rows_lds for FP16 storage).
+enum PullKind : int { kPullShifted = 0, kPullRows = 1, kPullFlat = 2 };
 
 template <int LAT, typename S, int PULL>
 __device__ inline void pull_aligned(const S *__restrict__ src, const Grid &g, const Cell &c, int32_t x, bool live,
@@ -222,13 +219,13 @@ __device__ inline void pull_rows_lds(const S *__restrict__ src, const Grid &g, c
     }
 }
 
-template <int LAT, typename S, int ORDER, int MODE, int PULL>
+template <int LAT, typename S, int ORDER, int MODE, int PULL, int AUX>
 __global__ __launch_bounds__(256) void k_step(const S *__restrict__ src, S *__restrict__ dst, const Grid g,
                                               const StepConsts<typename Conv<S>::C> k, const TileMap m,
                                               const uint32_t *__restrict__ links, const float *__restrict__ gray)
 {
     constexpr bool GENERAL = MODE == kLinks;
-    constexpr bool ALIGNED = PULL != kPullShifted;
+    constexpr bool ALIGNED = PULL == kPullRows;
     static_assert(!(ALIGNED && GENERAL), "the lane-exchange pull serves the periodic, gray and streaming steps");
     using L = Lattice<LAT>;
     constexpr PullOrder<LAT> kPull{};
@@ -236,9 +233,14 @@ __global__ __launch_bounds__(256) void k_step(const S *__restrict__ src, S *__re
     constexpr int NP = L::NP;
     const uint32_t t = tile_of(m, blockIdx.x);
     const uint32_t tx = t % m.tiles_x, tyz = t / m.tiles_x;
-    const int32_t x = (int32_t)(tx * blockDim.x + threadIdx.x);
-    const int32_t y = (int32_t)((tyz % m.tiles_y) * blockDim.y + threadIdx.y);
+    int32_t x = (int32_t)(tx * blockDim.x + threadIdx.x);
+    int32_t y = (int32_t)((tyz % m.tiles_y) * blockDim.y + threadIdx.y);
     const int32_t z = (int32_t)(tyz / m.tiles_y);
+    if constexpr (PULL == kPullFlat) {  // blockDim = 256 x 1, tiles_y = 1: x counts the cells of z-plane z
+        uint32_t xr;
+        y = (int32_t)div_by((uint32_t)x, m.mx, (uint32_t)g.nx, xr);
+        x = (int32_t)xr;
+    }
 
     C gp[NP + 1], gm[NP + 1];
     Cell c;
@@ -311,11 +313,11 @@ __global__ __launch_bounds__(256) void k_step(const S *__restrict__ src, S *__re
         }
     }
     const PlaneStores ps = plane_stores(dst, g, own_ref(c));
-    st_plane(ps, 0, Conv<S>::st(gp[0]));
+    st_plane_aux<AUX>(ps, 0, Conv<S>::st(gp[0]));
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-        st_plane(ps, 2 * p + 1, Conv<S>::st(gp[p + 1]));
-        st_plane(ps, 2 * p + 2, Conv<S>::st(gm[p + 1]));
+        st_plane_aux<AUX>(ps, 2 * p + 1, Conv<S>::st(gp[p + 1]));
+        st_plane_aux<AUX>(ps, 2 * p + 2, Conv<S>::st(gm[p + 1]));
     }
 }
 
@@ -1121,6 +1123,54 @@ template <int LAT, typename S, int M> unsigned step_lds(unsigned threads)
     return 0u;
 }
 
+// How a step is launched: its pull, whether its stores are cached (else non-temporal), and how many
+// consecutive tiles share an XCD (0: the tiles of a row).
+struct StepShape {
+    int pull;
+    bool cached;
+    uint32_t group;
+};
+
+// The rule behind it. All pulls compute the same state bit for bit. Us per step, D3Q19 unless
+// named otherwise:
+//  * Rows that are a multiple of 64 cells, up to 256 (and not the links step): the lane exchange.
+//    Its stores are whole cache lines; they stay in the caches where both population arrays come
+//    near the 256 MB Infinity Cache (80 to 400 MB: FP32 gray 128^3 52.8 -> 49.2, 192 x 128 x 100
+//    63.9 -> 58.0, FP16 128^3 27.6 -> 26.7), and go past them where the grid is larger (192^3 FP32
+//    gray 178.5 against 198.9 cached, FP64 gray 128^3 102.7 against 111.1) or smaller (64^3 FP32
+//    7.1 against 8.1).
+//  * Other row lengths leave lanes of a box idle and, where a row is no whole number of cache
+//    lines, parts of lines at both ends of every row: work-groups then take 256 consecutive
+//    cells whatever rows they lie in, and cached stores, 16 neighbouring tiles on one XCD, let
+//    its L2 put the lines together. Boxes with non-temporal stores -> runs with cached ones:
+//    FP16 129 x 100 x 90 26.3 -> 16.3, 250 x 190 x 130 104.5 -> 91.0; FP32 gray 129 x 100 x 90
+//    45.0 -> 29.3, 250 x 190 x 130 232.8 -> 179.2; D3Q27 BF16 155 x 197 x 157 128.2 -> 115.7; masked
+//    D3Q27 FP32 129 x 100 x 90 67.6 -> 50.8, FP16 45.4 -> 29.4. Runs with non-temporal stores are no
+//    better than boxes there (FP16 129 x 100 x 90 21.9). Rows of whole lines (96 cells in FP32) take
+//    them on large grids all the same, as above.
+//  * Longer rows of a multiple of 64 cells, and the links step on any multiple: boxes, shifted
+//    loads, non-temporal stores. In the links step the tiles of a row share an XCD: its shifted
+//    and bounce-back pulls read lines that they share, which the L2 then serves once (512^3
+//    porous medium FP16 2,778 -> 2,647, FP32 4,854 -> 4,812). 16-bit periodic and gray steps take 4
+//    tiles (FP16 320 x 200 x 100 88.8 -> 79.2, 512 x 128 x 128 108.6 -> 104.4), FP32 and FP64 the plain
+//    order (512 x 128 x 128 FP32 204.4 against 206.5; 512^3 3,377 against 3,484 with 2).
+// A launch that the caller has shaped (lbm_set_launch) keeps its boxes and non-temporal stores.
+StepShape step_shape(int mode, int lat, size_t bytes, const Grid &g, int block_x, int flags)
+{
+    const bool shaped = !(flags & kLaunchDefault);
+    const uint32_t group = mode == kLinks ? 0u : (bytes == 2 && !shaped ? 4u : 1u);
+    const double q = lat == kD2Q9 ? 9 : (lat == kD3Q19 ? 19 : 27);
+    const double both = 2.0 * q * (double)bytes * g.n;
+    const bool near = both >= 80e6 && both <= 400e6;
+    if (!shaped && g.nx % 64 != 0) {
+        const bool whole_lines = g.nx * bytes % 128 == 0;
+        return StepShape{kPullFlat, !whole_lines || both <= 400e6, 16u};
+    }
+    if (mode != kLinks && !(flags & kLaunchShiftedPull) && g.nx % 64 == 0 && block_x == g.nx)
+        return StepShape{kPullRows, !shaped && near, 1u};
+    return StepShape{kPullShifted, false, group};
+}
+
 hipError_t launch_step(int lattice, int storage, int order, const Grid &g, const StepConsts<double> &k64,
                        const StepConsts<float> &k32, const uint32_t *links, const float *gray, const void *src,
                        void *dst, int block_x, int block_y, int flags, hipStream_t stream)
@@ -1132,33 +1182,40 @@ hipError_t launch_step(int lattice, int storage, int order, const Grid &g, const
             constexpr int LAT = decltype(lat)::value;
             const StepConsts<C> *kc;
             if constexpr (sizeof(C) == 8) kc = &k64; else kc = &k32;
-            const dim3 g3 = cell_grid(g, block_x, block_y), block(block_x, block_y);
-            const unsigned threads = (unsigned)(block_x * block_y);
+            const int mode = (flags & kLaunchStreamOnly) ? kStream
+                             : gray ? kGray : ((links != nullptr || kc->forced) ? kLinks : kPlain);
+            const StepShape sh = step_shape(mode, LAT, sizeof(S), g, block_x, flags);
+            const dim3 block = sh.pull == kPullFlat ? dim3(256) : dim3(block_x, block_y);
+            const dim3 g3 = sh.pull == kPullFlat
+                                ? dim3(((uint32_t)g.nx * (uint32_t)g.ny + 255u) / 256u, 1u, (uint32_t)g.nz)
+                                : cell_grid(g, block_x, block_y);
             TileMap m;
             m.tiles_x = g3.x;
             m.tiles_y = g3.y;
             m.nblocks = g3.x * g3.y * g3.z;
             m.xcd_slabs = (flags & kLaunchXcdSlabs) ? 1u : 0u;
+            m.group = sh.group ? sh.group : g3.x;
+            m.mx = g.nx == 1 ? 0xffffffffu : (uint32_t)(4294967296ull / (uint64_t)g.nx);
             const dim3 grid(m.nblocks);
-            const int mode = (flags & kLaunchStreamOnly) ? kStream
-                             : gray ? kGray : ((links != nullptr || kc->forced) ? kLinks : kPlain);
-            m.row_xcd = mode == kLinks ? 1u : 0u;
-            // the lane-exchange pull needs work-groups of whole rows (see pull_aligned)
-            const bool aligned = mode != kLinks && !(flags & kLaunchShiftedPull) && g.nx % 64 == 0 &&
-                                 block_x == g.nx;
+            const unsigned threads = block.x * block.y;
             const S *in = (const S *)src;
             S *out = (S *)dst;
+#define LBM_LAUNCH(O, M, P, A)                                                                                     \
+    hipLaunchKernelGGL((k_step<LAT, S, O, M, P, A>), grid, block, (step_lds<LAT, S, M>(threads)), stream, in, out, g, \
+                       *kc, m, links, gray)
 #define LBM_STEP(O, M)                                                                                           \
     do {                                                                                                         \
+        if (sh.pull == kPullFlat) {                                                                              \
+            if (sh.cached) LBM_LAUNCH(O, M, kPullFlat, 0); else LBM_LAUNCH(O, M, kPullFlat, 2);                  \
+            break;                                                                                               \
+        }                                                                                                        \
         if constexpr (M != kLinks) {                                                                             \
-            if (aligned) {                                                                                       \
-                hipLaunchKernelGGL((k_step<LAT, S, O, M, kPullRows>), grid, block, (step_lds<LAT, S, M>(threads)),  \
-                                   stream, in, out, g, *kc, m, links, gray);                                     \
+            if (sh.pull == kPullRows) {                                                                          \
+                if (sh.cached) LBM_LAUNCH(O, M, kPullRows, 0); else LBM_LAUNCH(O, M, kPullRows, 2);              \
                 break;                                                                                           \
             }                                                                                                    \
         }                                                                                                        \
-        hipLaunchKernelGGL((k_step<LAT, S, O, M, kPullShifted>), grid, block, (step_lds<LAT, S, M>(threads)), stream, in, out, g, \
-                           *kc, m, links, gray);                                                                 \
+        LBM_LAUNCH(O, M, kPullShifted, 2);                                                                       \
     } while (0)
             if (mode == kStream) {
                 LBM_STEP(3, kStream);
@@ -1172,6 +1229,7 @@ hipError_t launch_step(int lattice, int storage, int order, const Grid &g, const
                 else LBM_STEP(3, kPlain);
             }
 #undef LBM_STEP
+#undef LBM_LAUNCH
             return hipGetLastError();
         });
     });

@@ -267,19 +267,21 @@ constexpr SweepTile kTiles[] = {
 
 // The cut of a grid into tiles and segments, from the time that a cut takes: rounds of one
 // work-group per compute unit x planes (two more than the segment's, for the rim) x rows. Measured
-// over grids of 30 x 25 x 40 to 256^3, even and odd, it is right to 5% for D3Q19 and 10% for D3Q27.
-// Against it stands the time of two single steps: 2 us a launch and the bytes at 6.3 TB/s, or 4.7
-// TB/s where rows are no whole cache lines (their stores then leave partial ones). The line so lies
-// near 80^3: below, the work-groups are too few and their rims too large (us per step, single against
-// sweep, D3Q19 FP32: 48^3 6.0 / 6.2, 64^3 8.05 / 7.8, 77 x 85 x 60 15.8 / 16.0, 96^3 25.2 / 22.3,
-// 150 x 101 x 75 34.9 / 30.3; D3Q27 FP32: 96^3 35.5 / 36.1, 128^3 73.8 / 66.8).
+// over grids of 40 x 40 x 500 to 256^3, even and odd, it is right to 10% or so. Against it stands
+// the time of two single steps: 2 us a launch and the bytes at 6.3 TB/s, or 5.4 TB/s where rows are
+// no whole cache lines and the caches no longer hold the state. The line so lies near 100^3: below,
+// the work-groups are too few and their rims too large (us per step, single against sweep,
+// D3Q19 FP32: 48^3 5.7 / 6.1, 100^3 24.3 / 28.4, 150 x 101 x 75 28.5 / 29.8, 128 x 96 x 80 24.7 / 20.8,
+// 200 x 150 x 100 80.7 / 68.7, 250 x 190 x 130 175.3 / 135.8; D3Q27 FP32: 100^3 34.0 / 46.3, 128^3
+// 73.6 / 63.0; D3Q19 FP64: 77 x 85 x 60 22.2 / 23.9, 110 x 120 x 100 78.7 / 56.6).
 SweepPlan plan_sweep(int lattice, int storage, const Grid &g)
 {
     SweepPlan best{0, 0, 0};
     const int bytes = storage == kF64 ? 8 : 4;
     const double q = lattice == kD3Q19 ? 19.0 : 27.0;
-    const double rate = g.nx * bytes % 128 == 0 ? 6.3e6 : 4.7e6;  // bytes per us
-    double best_us = 2.0 * (2.0 + 2.0 * q * bytes * g.n / rate) / 1.05;
+    const double both = 2.0 * q * bytes * g.n;  // bytes of a step
+    const double rate = both > 300e6 && g.nx * bytes % 128 != 0 ? 5.4e6 : 6.3e6;  // bytes per us
+    double best_us = 2.0 * (2.0 + both / rate) / 1.05;
     for (const SweepTile &t : kTiles) {
         if (t.lattice != lattice || t.storage != storage) continue;
         // D3Q19 FP64: rows of 32 cells where they are whole cache lines (256^3: 505 against 532 us),

@@ -1,6 +1,6 @@
 """The two-step pass of periodic three-dimensional grids: bit for bit two single steps, and the oracle.
 
-The library takes steps two at a time on grids of about 80^3 cells and more (an odd number ends
+The library takes steps two at a time on grids of about 100^3 cells and more (an odd number ends
 with a single step); a launch shape set by the caller keeps every step a single one. The grids here
 are the smallest of their kind on which the rule picks the two-step pass: rows shorter than a
 tile, ragged tiles in x and y, uneven z segments, and whole tiles.
@@ -25,12 +25,12 @@ def _need_gpu():
 
 
 @pytest.mark.parametrize("lattice,storage,shape,order,steps", [
-    ("D3Q19", "f32", (40, 41, 499), 3, 5),    # rows shorter than a tile, many uneven segments
+    ("D3Q19", "f32", (64, 299, 31), 3, 5),    # rows of one tile, uneven segments
     ("D3Q19", "f32", (192, 96, 64), 2, 6),    # whole cache lines, order 2
-    ("D3Q19", "f64", (500, 41, 43), 3, 5),    # 64-wide tiles, ragged in x and y
+    ("D3Q19", "f64", (45, 90, 250), 3, 5),    # rows shorter than a tile, 64-wide tiles ragged in y
     ("D3Q19", "f64", (96, 100, 97), 3, 4),    # 32-wide tiles
-    ("D3Q27", "f32", (129, 131, 60), 3, 5),   # a tile with one column
-    ("D3Q27", "f64", (130, 95, 83), 3, 5),
+    ("D3Q27", "f32", (200, 190, 99), 3, 5),   # ragged in x and y, two segments
+    ("D3Q27", "f64", (130, 111, 83), 3, 5),
 ])
 def test_two_step_pass_is_two_steps(lattice, storage, shape, order, steps):
     d = W.DIMS[lattice]
