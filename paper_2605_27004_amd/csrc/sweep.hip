@@ -14,7 +14,7 @@
 // two steps and cell, VALU 78% busy, the clock down to 1.7 GHz) and FP64 by HBM and LDS space (one
 // work-group of 10 waves per compute unit). Us per step, two single steps -> sweep:
 //   D3Q19 FP32 256^3 389.6 -> 262.5, 128^3 52.1 -> 38.4; FP64 256^3 808.9 -> 505.0,
-//   250 x 190 x 130 404.6 -> 216.4; D3Q27 FP32 256^3 564.8 -> 447.4, FP64 256^3 1191 -> 904.
+//   250 x 190 x 130 404.6 -> 193.1; D3Q27 FP32 256^3 564.8 -> 447.4, FP64 256^3 1191 -> 904.
 //
 //  * Lanes: wave w of the tile is one row of 64 cells (two of 32), so the stores of a wave are
 //    whole cache lines, and the columns left and right of the tile sit in the last waves. One flat
@@ -32,6 +32,7 @@
 
 #include "cell.hpp"
 #include "common.hpp"
+#include "sweep.hpp"
 
 #pragma clang fp contract(off)
 
@@ -40,66 +41,12 @@ namespace {
 
 using namespace cell;
 
-// Place in LDS of direction i among the directions with the same c_z; -1 for those that stay in
-// their column (c_x = c_y = 0: rest, +z, -z), which their lane keeps.
-template <int LAT> struct Ring {
-    int slot[Lattice<LAT>::Q];
-    int count[3];  // by c_z + 1
-    constexpr Ring() : slot(), count()
-    {
-        for (int i = 0; i < Lattice<LAT>::Q; ++i) {
-            const PairRow v = i == 0 ? PairRow{0, 0, 0} : Lattice<LAT>::pair((i - 1) / 2);
-            slot[i] = (v.cx == 0 && v.cy == 0) ? -1 : count[((i & 1) ? v.cz : -v.cz) + 1]++;
-        }
-    }
-};
-
-constexpr int cz_of(PairRow v, int i) { return (i & 1) ? v.cz : -v.cz; }
-
-// Raw buffer resource on a z-plane (the same for the whole work-group, see plane_stores): the q
-// pulls of a cell then take nine lane offsets and a scalar offset per direction, with no address
-// arithmetic per load.
-template <typename S> __device__ inline __amdgpu_buffer_rsrc_t plane_rsrc(const S *p)
-{
-    const uint64_t a = reinterpret_cast<uint64_t>(p);
-    const uint64_t u = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32)) << 32) |
-                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
-    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<S *>(u), (short)0, -1, 0x00020000);
-}
-
-template <typename S> __device__ inline S ld_buf(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t soff)
-{
-    if constexpr (sizeof(S) == 4)
-        return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, (int)soff, 0));
-    else
-        return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, (int)soff, 0));
-}
-
-// v[0] goes to the end, the others move down.
-template <typename P, int N> __device__ inline void rotate(P *(&v)[N])
-{
-    P *f = v[0];
-#pragma unroll
-    for (int j = 0; j + 1 < N; ++j) v[j] = v[j + 1];
-    v[N - 1] = f;
-}
-
-// Barrier that orders LDS only: the work-group's global loads and stores stay in flight across it.
-__device__ inline void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Two steps over the tile (tx, ty) of TX columns by ty_cells rows (at most TYM) and the z-planes of
-// one of `segs` segments. The second step of plane z needs the first step's values of planes z - 1
-// (c_z = +1), z (c_z = 0) and z + 1 (c_z = -1). REGS: each lane reads its neighbours' values as
-// soon as a plane is there and keeps them in registers until their turn, so LDS holds one plane,
-// twice (one barrier per plane); else LDS holds the planes until their turn (three, two and one of
-// them, two barriers per plane), for FP64, whose registers would spill (505 against 570 us at
-// D3Q19 256^3; FP32 the other way round, 265 against 285 us).
-template <int LAT, typename S, int ORDER, int TX, int TYM, bool REGS>
+// one of `segs` segments. AUX: cache policy of the stores. Rows of whole cache lines are written
+// non-temporally (256^3 FP32 266 against 275 us cached); other rows leave parts of lines at both ends of a
+// tile's rows, which cached stores let the L2 put together (250 x 190 x 130 FP32 135.6 -> 120.6, FP64
+// 218.9 -> 193.1, D3Q27 FP64 170 x 160 x 150 295.5 -> 257.1).
+template <int LAT, typename S, int ORDER, int TX, int TYM, bool REGS, int AUX>
 __global__ __launch_bounds__(((TX + 2) * (TYM + 2) + 63) / 64 * 64) void k_sweep(
     const S *__restrict__ src, S *__restrict__ dst, const Grid g, const StepConsts<typename Conv<S>::C> k,
     const int ty_cells, const uint32_t tiles_x, const uint32_t tiles, const uint32_t segs)
@@ -107,10 +54,8 @@ __global__ __launch_bounds__(((TX + 2) * (TYM + 2) + 63) / 64 * 64) void k_sweep
     using L = Lattice<LAT>;
     using C = typename Conv<S>::C;
     constexpr int NP = L::NP, W = TX + 2, COLS = W * (TYM + 2);
-    constexpr Ring<LAT> R{};
     constexpr PullOrder<LAT> kPull{};
-    constexpr int NU = REGS ? 2 : 3, NF = 2, ND = REGS ? 2 : 1;  // planes of c_z = +1, 0, -1 values in LDS
-    __shared__ S lds[(NU * R.count[2] + NF * R.count[1] + ND * R.count[0]) * COLS];
+    __shared__ S lds[sweep::ring_values<LAT, REGS>() * COLS];
 
     // lanes 0 .. TX H - 1: the tile's own x, row by row; then the columns left and right of it
     const int H = ty_cells + 2, IN = TX * H;
@@ -125,17 +70,6 @@ __global__ __launch_bounds__(((TX + 2) * (TYM + 2) + 63) / 64 * 64) void k_sweep
         hx = (h & 1) ? W - 1 : 0;
         hy = h >> 1;
     }
-    // LDS places of this column, [0] the plane read, the last one the plane written
-    S *up[NU], *flat[NF], *down[ND];
-    {
-        S *p = lds + hy * W + hx;
-#pragma unroll
-        for (int j = 0; j < NU; ++j, p += R.count[2] * COLS) up[j] = p;
-#pragma unroll
-        for (int j = 0; j < NF; ++j, p += R.count[1] * COLS) flat[j] = p;
-#pragma unroll
-        for (int j = 0; j < ND; ++j, p += R.count[0] * COLS) down[j] = p;
-    }
     const uint32_t step = g.bc * (uint32_t)sizeof(S);
 
     // consecutive tiles of a segment on one XCD
@@ -145,8 +79,7 @@ __global__ __launch_bounds__(((TX + 2) * (TYM + 2) + 63) / 64 * 64) void k_sweep
     const int z_begin = (int)((uint64_t)g.nz * seg / segs), z_end = (int)((uint64_t)g.nz * (seg + 1u) / segs);
     const int xo = (int)(tile % tiles_x) * TX + hx - 1, yo = (int)(tile / tiles_x) * ty_cells + hy - 1;
     const bool inner = t < IN && hy >= 1 && hy <= ty_cells && xo < g.nx && yo < g.ny;
-    int z = z_begin == 0 ? g.nz - 1 : z_begin - 1;
-    const Cell c = cell_of(g, (xo + g.nx) % g.nx, (yo + g.ny) % g.ny, z);
+    const Cell c = cell_of(g, (xo + g.nx) % g.nx, (yo + g.ny) % g.ny, 0);
     // in-plane byte offsets of the nine columns a pull reads
     uint32_t off[3][3];
 #pragma unroll
@@ -154,92 +87,36 @@ __global__ __launch_bounds__(((TX + 2) * (TYM + 2) + 63) / 64 * 64) void k_sweep
 #pragma unroll
         for (int cx = -1; cx <= 1; ++cx)
             off[cy + 1][cx + 1] = (c.at + back(c.ox, cx) + back(c.oy, cy)) * (uint32_t)sizeof(S);
-
-    S pre[L::Q];
-    auto load = [&](int zz) {
-        const __amdgpu_buffer_rsrc_t r0 = plane_rsrc(src + (uint64_t)zz * g.zs);
-        const __amdgpu_buffer_rsrc_t rm = plane_rsrc(src + (uint64_t)(zz == 0 ? g.nz - 1 : zz - 1) * g.zs);
-        const __amdgpu_buffer_rsrc_t rp = plane_rsrc(src + (uint64_t)(zz == g.nz - 1 ? 0 : zz + 1) * g.zs);
+    // plane `it` of the walk: z_begin - 1 + it, periodic
+    const auto plane_at = [&](int it) {
+        const int z = z_begin - 1 + it;
+        return z < 0 ? z + g.nz : (z >= g.nz ? z - g.nz : z);
+    };
+    const auto load = [&](int it, S *pre) {
+        const int z = plane_at(it);
+        const __amdgpu_buffer_rsrc_t r0 = sweep::plane_rsrc(src + (uint64_t)z * g.zs);
+        const __amdgpu_buffer_rsrc_t rm = sweep::plane_rsrc(src + (uint64_t)(z == 0 ? g.nz - 1 : z - 1) * g.zs);
+        const __amdgpu_buffer_rsrc_t rp = sweep::plane_rsrc(src + (uint64_t)(z == g.nz - 1 ? 0 : z + 1) * g.zs);
 #pragma unroll
         for (int j = 0; j < L::Q; ++j) {
             const int i = kPull.dir[j];
             const PairRow v = i == 0 ? PairRow{0, 0, 0} : L::pair((i - 1) / 2);
             const int sg = (i & 1) ? 1 : -1, cz = sg * v.cz;
-            pre[i] = ld_buf<S>(cz > 0 ? rm : (cz < 0 ? rp : r0), off[sg * v.cy + 1][sg * v.cx + 1],
-                               (uint32_t)i * step);
+            pre[i] = sweep::ld_buf<S>(cz > 0 ? rm : (cz < 0 ? rp : r0), off[sg * v.cy + 1][sg * v.cx + 1],
+                                      (uint32_t)i * step);
         }
     };
-    load(z);
-
-    // values waiting for their plane's second step: w1 one plane old (c_z = 0 and +1), w2 two (+1)
-    C w1[L::Q], w2[L::Q];
-#pragma unroll
-    for (int i = 0; i < L::Q; ++i) w1[i] = w2[i] = C(0);
-    const int count = z_end - z_begin + 2;
-    for (int it = 0; it < count; ++it) {
-        C gp[NP + 1], gm[NP + 1];
-        gp[0] = Conv<S>::ld(pre[0]);
+    const auto store = [&](int it, const C *gp, const C *gm) {
+        const PlaneStores ps = plane_stores(dst, g, Ref{(uint64_t)plane_at(it - 1) * g.zs, c.at});
+        st_plane_aux<AUX>(ps, 0, Conv<S>::st(gp[0]));
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-            gp[p + 1] = Conv<S>::ld(pre[2 * p + 1]);
-            gm[p + 1] = Conv<S>::ld(pre[2 * p + 2]);
+            st_plane_aux<AUX>(ps, 2 * p + 1, Conv<S>::st(gp[p + 1]));
+            st_plane_aux<AUX>(ps, 2 * p + 2, Conv<S>::st(gm[p + 1]));
         }
-        const int below = z == 0 ? g.nz - 1 : z - 1;  // the plane the second step writes
-        z = z == g.nz - 1 ? 0 : z + 1;
-        if (it + 1 < count) load(z);
-        __builtin_amdgcn_sched_barrier(0);
-        collide_cell<LAT, ORDER, false, C, kClose<S>>(k, gp, gm);
-        C now[L::Q];
-#pragma unroll
-        for (int i = 0; i < L::Q; ++i) {
-            const S val = Conv<S>::st(i == 0 ? gp[0] : ((i & 1) ? gp[(i - 1) / 2 + 1] : gm[(i - 1) / 2 + 1]));
-            const int cz = i == 0 ? 0 : cz_of(L::pair((i - 1) / 2), i);
-            if (R.slot[i] < 0)
-                now[i] = Conv<S>::ld(val);
-            else if (column)
-                (cz > 0 ? up[NU - 1] : (cz == 0 ? flat[NF - 1] : down[ND - 1]))[R.slot[i] * COLS] = val;
-        }
-        lds_barrier();
-        if (inner) {
-            constexpr int RU = REGS ? NU - 1 : 0, RF = REGS ? NF - 1 : 0, RD = ND - 1;
-#pragma unroll
-            for (int i = 0; i < L::Q; ++i) {
-                const PairRow v = i == 0 ? PairRow{0, 0, 0} : L::pair((i - 1) / 2);
-                const int sg = (i & 1) ? 1 : -1, cz = sg * v.cz;
-                if (R.slot[i] >= 0)
-                    now[i] = Conv<S>::ld((cz > 0 ? up[RU] : (cz == 0 ? flat[RF] : down[RD]))
-                                             [R.slot[i] * COLS - sg * v.cx - sg * v.cy * W]);
-            }
-#pragma unroll
-            for (int i = 0; i < L::Q; ++i) {
-                const int cz = i == 0 ? 0 : cz_of(L::pair((i - 1) / 2), i);
-                const bool wait = REGS || R.slot[i] < 0;
-                const C val = !wait || cz < 0 ? now[i] : (cz == 0 ? w1[i] : w2[i]);
-                if (wait && cz > 0) w2[i] = w1[i];
-                if (wait && cz >= 0) w1[i] = now[i];
-                if (i == 0) gp[0] = val;
-                else if (i & 1) gp[(i - 1) / 2 + 1] = val;
-                else gm[(i - 1) / 2 + 1] = val;
-            }
-            collide_cell<LAT, ORDER, false, C, kClose<S>>(k, gp, gm);
-        }
-        // the next plane's loads end here, before this plane's stores are issued
-#pragma unroll
-        for (int i = 0; i < L::Q; ++i) asm volatile("" : "+v"(pre[i]));
-        if (it >= 2 && inner) {
-            const PlaneStores ps = plane_stores(dst, g, Ref{(uint64_t)below * g.zs, c.at});
-            st_plane(ps, 0, Conv<S>::st(gp[0]));
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                st_plane(ps, 2 * p + 1, Conv<S>::st(gp[p + 1]));
-                st_plane(ps, 2 * p + 2, Conv<S>::st(gm[p + 1]));
-            }
-        }
-        if (!REGS) lds_barrier();
-        rotate(up);
-        rotate(flat);
-        rotate(down);
-    }
+    };
+    sweep::planes<LAT, S, ORDER, REGS, COLS>(
+        lds, hy * W + hx, column, inner, z_end - z_begin + 2, k, load, [](int cx, int cy) { return cx + cy * W; }, store);
 }
 
 }  // namespace
@@ -272,7 +149,7 @@ constexpr SweepTile kTiles[] = {
 // no whole cache lines and the caches no longer hold the state. The line so lies near 100^3: below,
 // the work-groups are too few and their rims too large (us per step, single against sweep,
 // D3Q19 FP32: 48^3 5.7 / 6.1, 100^3 24.3 / 28.4, 150 x 101 x 75 28.5 / 29.8, 128 x 96 x 80 24.7 / 20.8,
-// 200 x 150 x 100 80.7 / 68.7, 250 x 190 x 130 175.3 / 135.8; D3Q27 FP32: 100^3 34.0 / 46.3, 128^3
+// 200 x 150 x 100 80.7 / 68.7, 250 x 190 x 130 175.3 / 120.6; D3Q27 FP32: 100^3 34.0 / 46.3, 128^3
 // 73.6 / 63.0; D3Q19 FP64: 77 x 85 x 60 22.2 / 23.9, 110 x 120 x 100 78.7 / 56.6).
 SweepPlan plan_sweep(int lattice, int storage, const Grid &g)
 {
@@ -311,14 +188,19 @@ hipError_t launch_sweep(int lattice, int storage, int order, const Grid &g, cons
     const uint32_t tiles = tiles_x * tiles_y;
     const dim3 grid(tiles * (uint32_t)p.segs);
     const dim3 block((uint32_t)((p.tx + 2) * (p.ty + 2) + 63) / 64 * 64);
-#define LBM_SWEEP(LAT, S, TX, TYM, REGS, KC)                                                                       \
+    const bool whole_lines = g.nx * (storage == kF64 ? 8 : 4) % 128 == 0;
+#define LBM_SWEEP_A(LAT, S, O, TX, TYM, REGS, AUX, KC)                                                           \
+    hipLaunchKernelGGL((k_sweep<LAT, S, O, TX, TYM, REGS, AUX>), grid, block, 0, stream, (const S *)src, (S *)dst, g, \
+                       KC, p.ty, tiles_x, tiles, (uint32_t)p.segs)
+#define LBM_SWEEP(LAT, S, TX, TYM, REGS, KC)                                                                     \
     do {                                                                                                         \
-        if (order == 2)                                                                                          \
-            hipLaunchKernelGGL((k_sweep<LAT, S, 2, TX, TYM, REGS>), grid, block, 0, stream, (const S *)src,        \
-                               (S *)dst, g, KC, p.ty, tiles_x, tiles, (uint32_t)p.segs);                         \
-        else                                                                                                     \
-            hipLaunchKernelGGL((k_sweep<LAT, S, 3, TX, TYM, REGS>), grid, block, 0, stream, (const S *)src,        \
-                               (S *)dst, g, KC, p.ty, tiles_x, tiles, (uint32_t)p.segs);                         \
+        if (order == 2) {                                                                                        \
+            if (whole_lines) LBM_SWEEP_A(LAT, S, 2, TX, TYM, REGS, 2, KC);                                       \
+            else LBM_SWEEP_A(LAT, S, 2, TX, TYM, REGS, 0, KC);                                                   \
+        } else {                                                                                                 \
+            if (whole_lines) LBM_SWEEP_A(LAT, S, 3, TX, TYM, REGS, 2, KC);                                       \
+            else LBM_SWEEP_A(LAT, S, 3, TX, TYM, REGS, 0, KC);                                                   \
+        }                                                                                                        \
         return hipGetLastError();                                                                                \
     } while (0)
     if (lattice == kD3Q19 && storage == kF32) LBM_SWEEP(kD3Q19, float, 64, 13, true, k32);
@@ -327,6 +209,7 @@ hipError_t launch_sweep(int lattice, int storage, int order, const Grid &g, cons
     if (lattice == kD3Q27 && storage == kF32) LBM_SWEEP(kD3Q27, float, 64, 9, true, k32);
     if (lattice == kD3Q27 && storage == kF64) LBM_SWEEP(kD3Q27, double, 32, 10, false, k64);
 #undef LBM_SWEEP
+#undef LBM_SWEEP_A
     return hipErrorInvalidValue;
 }
 
