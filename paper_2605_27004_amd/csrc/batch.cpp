@@ -170,10 +170,12 @@ struct lbm_batch {
     uint32_t spin_limit;
     lbm_batch_schedule sched;
     uint32_t nlaunch;        // tiles in the launch order
+    uint32_t nsweep;         // records of the two-step launch in dlaunch's place (0: single steps only)
     uint32_t nwg;            // persistent work-groups
     uint32_t max_chunks;     // largest items-per-domain count of the persistent lists
     // host copies of the schedule (kept alive across the uploads)
     std::vector<TileRec> launch;
+    std::vector<BatchSweepRec> sweep;
     std::vector<BatchItem> items;
     std::vector<uint32_t> wg_first, chunks;
 };
@@ -238,6 +240,56 @@ void build_launch_order(lbm_batch *b, bool xcd)
                 b->launch.push_back(j < queue[(size_t)k].size() ? queue[(size_t)k][j] : TileRec{kPadTile, 0});
     }
     b->nlaunch = (uint32_t)b->launch.size();
+}
+
+// The two-step launch's records, largest first (work-groups start in this order, so the last to
+// run are the shortest); none where two single steps are the faster way or a domain's rows are too
+// long. A record takes (planes + 2) x (waves of its rows) x row_us; the z-planes of a domain are cut into
+// runs of at most `len` planes, the len of least time over the compute units. Against that stands
+// the single step: 2 us a launch and the bytes at 6.1 TB/s. So many small domains sweep and a few do
+// not (us per step, single against sweep, D3Q19 FP32: 128 domains of 16 to 64 cells a side 210 / 173, 64
+// of 10 to 40 29.6 / 29.1, 22 of 15 to 46 21.3 / 22.0).
+std::vector<BatchSweepRec> plan_sweeps(const Plan &pl, int cu_count)
+{
+    std::vector<BatchSweepRec> best;
+    const int cols = batch_sweep_columns(pl.lattice, pl.storage);
+    if (cols == 0) return best;
+    double bytes = 0.0;
+    for (const BatchDomain &d : pl.dom) {
+        if ((int64_t)d.g.nx * std::min(d.g.ny, 4) > cols) return best;
+        bytes += 2.0 * pl.q * pl.bytes * d.cells;
+    }
+    const double row_us = 0.42 * (pl.q / 19.0) * (pl.bytes == 8 ? 1.72 : 1.0);
+    double best_us = 2.0 * (2.0 + bytes / 6.1e6) / 1.05;
+    for (int len : {64, 48, 32, 24, 16, 12, 8, 6, 4}) {
+        std::vector<std::pair<double, BatchSweepRec>> jobs;
+        double total = 0.0, most = 0.0;
+        for (size_t i = 0; i < pl.dom.size(); ++i) {
+            const Grid &g = pl.dom[i].g;
+            const bool whole = (int64_t)g.nx * g.ny <= cols;
+            const int tiles = whole ? 1 : (g.ny + cols / g.nx - 3) / (cols / g.nx - 2);
+            const int rows = whole ? g.ny : (g.ny + tiles - 1) / tiles;
+            const int segs = (g.nz + len - 1) / len;
+            for (int s = 0; s < segs; ++s)
+                for (int t = 0; t < tiles; ++t) {
+                    const int y0 = t * rows;
+                    if (y0 >= g.ny) break;
+                    const BatchSweepRec r{(uint32_t)i, y0, rows, (int32_t)((int64_t)g.nz * s / segs),
+                                          (int32_t)((int64_t)g.nz * (s + 1) / segs), 0u};
+                    const double us = (r.z1 - r.z0 + 2) * (double)((g.nx * (whole ? rows : rows + 2) + 63) / 64) * row_us;
+                    total += us;
+                    most = std::max(most, us);
+                    jobs.emplace_back(us, r);
+                }
+        }
+        const double us = 3.0 + std::max(total / cu_count + 0.3 * most, most);
+        if (us >= best_us || jobs.size() > 2 * pl.tiles.size()) continue;
+        best_us = us;
+        std::stable_sort(jobs.begin(), jobs.end(), [](const auto &a, const auto &b) { return a.first > b.first; });
+        best.clear();
+        for (const auto &j : jobs) best.push_back(j.second);
+    }
+    return best;
 }
 
 // Work lists of the persistent schedule: items in the order each work-group runs them.
@@ -363,7 +415,13 @@ int apply_schedule(lbm_batch *b, const lbm_batch_schedule &s)
     if (s.xcd_group != 0 && s.xcd_group != 1) return fail(LBM_ERR_ARG, "xcd_group must be 0 or 1");
     if (s.mode == LBM_BATCH_STEPWISE) {
         build_launch_order(b, s.xcd_group != 0);
-        int rc = upload(b, b->dlaunch, b->launch.data(), b->launch.size() * sizeof(TileRec));
+        b->sweep.clear();
+        if (!s.xcd_group) b->sweep = plan_sweeps(b->pl, b->cu_count);
+        b->nsweep = (uint32_t)b->sweep.size();
+        // the records take the place of the launch order, which is then the natural one (dtiles)
+        const int rc = b->nsweep
+                           ? upload(b, b->dlaunch, b->sweep.data(), b->sweep.size() * sizeof(BatchSweepRec))
+                           : upload(b, b->dlaunch, b->launch.data(), b->launch.size() * sizeof(TileRec));
         if (rc) return rc;
     } else {
         int rc = check_persistent(s);
@@ -390,11 +448,17 @@ int run_steps(lbm_batch *b, int64_t nsteps)
 {
     const Plan &pl = b->pl;
     if (b->sched.mode == LBM_BATCH_STEPWISE) {
-        for (int64_t i = 0; i < nsteps; ++i) {
-            const hipError_t e = launch_batch_step(pl.lattice, pl.storage, pl.order, b->nlaunch, b->dlaunch, b->ddom,
-                                                   b->dk64, b->dk32, b->pop[b->cur], b->pop[1 - b->cur], b->stream);
+        for (int64_t left = nsteps; left > 0;) {
+            const bool two = b->nsweep && left >= 2;
+            const hipError_t e =
+                two ? launch_batch_sweep(pl.lattice, pl.storage, pl.order, b->nsweep, (const BatchSweepRec *)b->dlaunch,
+                                         b->ddom, b->dk64, b->dk32, b->pop[b->cur], b->pop[1 - b->cur], b->stream)
+                    : launch_batch_step(pl.lattice, pl.storage, pl.order, b->nlaunch, b->nsweep ? b->dtiles : b->dlaunch,
+                                        b->ddom, b->dk64, b->dk32, b->pop[b->cur], b->pop[1 - b->cur],
+                                        2 * pl.pop_elems * pl.bytes <= 300000000, b->stream);
             if (e != hipSuccess) return fail_hip(e, "batch step launch");
             b->cur = 1 - b->cur;
+            left -= two ? 2 : 1;
         }
         return LBM_OK;
     }

@@ -38,8 +38,8 @@ __device__ inline FlatCell batch_cell(const BatchDomain &dm, uint32_t n)
     return flat_cell_of(dm.g, x, y, z);
 }
 
-// One periodic cell update: q pulls, the collision, q streaming stores.
-template <int LAT, typename S, int ORDER>
+// One periodic cell update: q pulls, the collision, q stores of cache policy AUX.
+template <int LAT, typename S, int ORDER, int AUX>
 __device__ inline void step_cell(const S *__restrict__ src, S *__restrict__ dst, const Grid &g, const FlatCell &c,
                                  const StepConsts<typename Conv<S>::C> &k)
 {
@@ -59,15 +59,15 @@ __device__ inline void step_cell(const S *__restrict__ src, S *__restrict__ dst,
     }
     collide_cell<LAT, ORDER, false, C, kClose<S>>(k, gp, gm);
     const PlaneStores ps = plane_stores(dst, g, own_ref(c));
-    st_plane(ps, 0, Conv<S>::st(gp[0]));
+    st_plane_aux<AUX>(ps, 0, Conv<S>::st(gp[0]));
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-        st_plane(ps, 2 * p + 1, Conv<S>::st(gp[p + 1]));
-        st_plane(ps, 2 * p + 2, Conv<S>::st(gm[p + 1]));
+        st_plane_aux<AUX>(ps, 2 * p + 1, Conv<S>::st(gp[p + 1]));
+        st_plane_aux<AUX>(ps, 2 * p + 2, Conv<S>::st(gm[p + 1]));
     }
 }
 
-template <int LAT, typename S, int ORDER>
+template <int LAT, typename S, int ORDER, int AUX>
 __global__ __launch_bounds__(kTileCells) void k_batch_step(const S *__restrict__ src, S *__restrict__ dst,
                                                            const TileRec *__restrict__ tiles,
                                                            const BatchDomain *__restrict__ doms,
@@ -79,7 +79,7 @@ __global__ __launch_bounds__(kTileCells) void k_batch_step(const S *__restrict__
     const uint32_t n = t.first + threadIdx.x;
     if (n >= dm.cells) return;
     const StepConsts<typename Conv<S>::C> k = kc[t.dom];
-    step_cell<LAT, S, ORDER>(src + dm.base, dst + dm.base, dm.g, batch_cell(dm, n), k);
+    step_cell<LAT, S, ORDER, AUX>(src + dm.base, dst + dm.base, dm.g, batch_cell(dm, n), k);
 }
 
 // ---- the persistent launch ------------------------------------------------------------------
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kTileCells) void k_batch_persist(
                 const BatchDomain dm = doms[dom];
                 const StepConsts<C> k = kc[dom];
                 for (uint32_t off = threadIdx.x; off < count; off += kTileCells)
-                    step_cell<LAT, S, ORDER>(src + dm.base, dst + dm.base, dm.g, batch_cell(dm, first + off), k);
+                    step_cell<LAT, S, ORDER, 2>(src + dm.base, dst + dm.base, dm.g, batch_cell(dm, first + off), k);
                 arrive(ctr + dom);
             }
         }
@@ -357,7 +357,7 @@ hipError_t launch_batch_init(int lattice, int storage, int order, uint32_t ntile
 
 hipError_t launch_batch_step(int lattice, int storage, int order, uint32_t ntiles, const TileRec *tiles,
                              const BatchDomain *doms, const StepConsts<double> *k64, const StepConsts<float> *k32,
-                             const void *src, void *dst, hipStream_t stream)
+                             const void *src, void *dst, bool cached, hipStream_t stream)
 {
     if (ntiles == 0) return hipSuccess;
     return by_lattice(lattice, [&](auto lat) {
@@ -371,8 +371,12 @@ hipError_t launch_batch_step(int lattice, int storage, int order, uint32_t ntile
                 // LDS); 512 D3Q19 FP32 domains 817 -> 785 us per step at 4 (3: 842, 5: 802)
                 constexpr bool wide = std::is_same<S, float>::value || std::is_same<S, double>::value;
                 const unsigned lds = wide ? stream_lds(Lattice<decltype(lat)::value>::Q, sizeof(S)) : 0u;
-                hipLaunchKernelGGL((k_batch_step<decltype(lat)::value, S, decltype(ord)::value>), dim3(ntiles),
-                                   dim3(kTileCells), lds, stream, (const S *)src, (S *)dst, tiles, doms, kc);
+                if (cached)
+                    hipLaunchKernelGGL((k_batch_step<decltype(lat)::value, S, decltype(ord)::value, 0>), dim3(ntiles),
+                                       dim3(kTileCells), lds, stream, (const S *)src, (S *)dst, tiles, doms, kc);
+                else
+                    hipLaunchKernelGGL((k_batch_step<decltype(lat)::value, S, decltype(ord)::value, 2>), dim3(ntiles),
+                                       dim3(kTileCells), lds, stream, (const S *)src, (S *)dst, tiles, doms, kc);
                 return hipGetLastError();
             });
         });
