@@ -168,6 +168,7 @@ struct lbm_batch {
     int64_t t;
     int cu_count;
     uint32_t spin_limit;
+    bool unchecked;          // a persistent launch ran since the status word was last read
     lbm_batch_schedule sched;
     uint32_t nlaunch;        // tiles in the launch order
     uint32_t nsweep;         // records of the two-step launch in dlaunch's place (0: single steps only)
@@ -482,6 +483,7 @@ int run_steps(lbm_batch *b, int64_t nsteps)
         a.ctr = b->dctr;
         a.status = b->dstatus;
         a.spin_limit = b->spin_limit;
+        b->unchecked = true;
         e = launch_batch_persist(pl.lattice, pl.storage, pl.order, b->nwg, a, b->stream);
         if (e != hipSuccess) return fail_hip(e, "persistent batch launch");
         b->cur = (int)((b->cur + n) & 1);
@@ -490,6 +492,7 @@ int run_steps(lbm_batch *b, int64_t nsteps)
     return LBM_OK;
 }
 
+// Read the status word, which only persistent launches raise (see `unchecked`); synchronises.
 int check_status(lbm_batch *b)
 {
     hipError_t e = hipStreamSynchronize(b->stream);
@@ -497,6 +500,7 @@ int check_status(lbm_batch *b)
     uint32_t st = 0;
     e = hipMemcpy(&st, b->dstatus, sizeof st, hipMemcpyDeviceToHost);
     if (e != hipSuccess) return fail_hip(e, "hipMemcpy");
+    b->unchecked = false;
     if (st != 0) {
         e = launch_fill_u32(b->dstatus, 1, b->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
@@ -607,6 +611,7 @@ int lbm_batch_init(lbm_batch **out, const lbm_batch_params *p, void *pop_a, void
     b->stream = (hipStream_t)hip_stream;
     b->t = 0;
     b->spin_limit = kDefaultSpinLimit;
+    b->unchecked = false;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&b->cu_count, hipDeviceAttributeMultiprocessorCount, dev);
@@ -761,18 +766,21 @@ int lbm_batch_autotune(lbm_batch *b, void *backup, int32_t trial_steps, lbm_batc
 int lbm_batch_moments(lbm_batch *b, double *rho, double *s, double *totals)
 {
     if (!b) return fail(LBM_ERR_ARG, "batch is NULL");
-    int rc = check_status(b);
+    const int rc = b->unchecked ? check_status(b) : LBM_OK;
     if (rc) return rc;
     const Plan &pl = b->pl;
+    const size_t bytes = pl.dom.size() * 4 * sizeof(double);
+    HostSlot slot(totals ? bytes : SIZE_MAX);
     hipError_t e = launch_batch_moments(pl.lattice, pl.storage, (uint32_t)pl.tiles.size(), b->dtiles, b->ddom,
                                         b->dk64, b->pop[b->cur], rho, s, (uint64_t)pl.cells, b->dpart,
-                                        (uint32_t)pl.dom.size(), b->dtot, b->stream);
+                                        (uint32_t)pl.dom.size(), slot.p ? slot.p : b->dtot, b->stream);
     if (e != hipSuccess) return fail_hip(e, "batch moments launch");
     if (!totals) return LBM_OK;
     std::vector<double> h(pl.dom.size() * 4);
-    e = hipMemcpyAsync(h.data(), b->dtot, h.size() * sizeof(double), hipMemcpyDeviceToHost, b->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
+    if (!slot.p) e = hipMemcpyAsync(h.data(), b->dtot, bytes, hipMemcpyDeviceToHost, b->stream);
+    if (e == hipSuccess) e = slot.wait(b->stream);
     if (e != hipSuccess) return fail_hip(e, "totals copy");
+    if (slot.p) std::memcpy(h.data(), slot.p, bytes);
     for (size_t d = 0; d < pl.dom.size(); ++d) {
         totals[4 * d + 0] = (double)pl.dom[d].cells * pl.rho0 + h[4 * d + 0];
         for (int a = 1; a < 4; ++a) totals[4 * d + a] = h[4 * d + a];
@@ -786,7 +794,7 @@ int lbm_batch_moments(lbm_batch *b, double *rho, double *s, double *totals)
 int lbm_batch_get_f64(lbm_batch *b, double *out)
 {
     if (!b || !out) return fail(LBM_ERR_ARG, "NULL argument");
-    int rc = check_status(b);
+    const int rc = b->unchecked ? check_status(b) : LBM_OK;
     if (rc) return rc;
     const Plan &pl = b->pl;
     const hipError_t e = launch_batch_export(pl.lattice, pl.storage, (uint32_t)pl.tiles.size(), b->dtiles, b->ddom,

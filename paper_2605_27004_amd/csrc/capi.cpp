@@ -7,6 +7,7 @@
 #include <cstdio>
 #include <cstring>
 #include <algorithm>
+#include <mutex>
 #include <new>
 #include <string>
 
@@ -35,6 +36,59 @@ int fail(int code, const char *fmt, ...)
 int fail_hip(hipError_t e, const char *what)
 {
     return fail(LBM_ERR_HIP, "%s: %s (%d)", what, hipGetErrorString(e), (int)e);
+}
+
+// ---- pinned places for totals ----------------------------------------------------------
+
+namespace {
+
+constexpr int kSlots = 16;
+constexpr size_t kSlotBytes = 32768;
+std::mutex g_slots_lock;
+char *g_slots = nullptr;
+bool g_slots_tried = false;
+uint32_t g_slots_taken = 0;  // bit i: place i belongs to a call
+
+}  // namespace
+
+HostSlot::HostSlot(size_t bytes) : p(nullptr), at_(-1)
+{
+    if (bytes > kSlotBytes) return;
+    std::lock_guard<std::mutex> guard(g_slots_lock);
+    if (!g_slots_tried) {
+        g_slots_tried = true;
+        void *block = nullptr;
+        // another thread may be recording a graph, which an allocation in the default mode would end
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (hipHostMalloc(&block, kSlots * kSlotBytes, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
+            g_slots = (char *)block;
+        else
+            (void)hipGetLastError();
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    if (!g_slots) return;
+    for (int i = 0; i < kSlots; ++i)
+        if (!(g_slots_taken >> i & 1u)) {
+            g_slots_taken |= 1u << i;
+            at_ = i;
+            p = (double *)(g_slots + i * kSlotBytes);
+            return;
+        }
+}
+
+HostSlot::~HostSlot()
+{
+    if (at_ < 0) return;
+    std::lock_guard<std::mutex> guard(g_slots_lock);
+    g_slots_taken &= ~(1u << at_);
+}
+
+hipError_t HostSlot::wait(hipStream_t stream)
+{
+    const hipError_t e = hipStreamSynchronize(stream);
+    if (e != hipSuccess) at_ = -1;
+    return e;
 }
 
 // ---- lattice tables in canonical order -------------------------------------------------
@@ -523,7 +577,7 @@ int lbm_moments(lbm_ctx *c, double *rho, double *s, double *totals)
 {
     if (!c) return fail(LBM_ERR_ARG, "ctx is NULL");
     const uint32_t nb = moments_groups(c->grid);
-    return moments_with(c, rho, s, totals, c->partials, c->partials + kPartials * (size_t)nb);
+    return moments_with(c, rho, s, totals, c->partials, c->partials + kPartials * (size_t)nb, true);
 }
 
 }  // extern "C"
@@ -531,15 +585,21 @@ int lbm_moments(lbm_ctx *c, double *rho, double *s, double *totals)
 namespace lbm {
 namespace host {
 
-int moments_with(lbm_ctx *c, double *rho, double *s, double *totals, double *partials, double *dtot)
+int moments_with(lbm_ctx *c, double *rho, double *s, double *totals, double *partials, double *dtot, bool pinned)
 {
+    double h[kPartials];
+    HostSlot slot(totals && pinned ? sizeof h : SIZE_MAX);
     hipError_t e = launch_moments(c->p.lattice, c->p.storage, c->grid, c->k64, c->links, c->pop[c->cur], rho, s,
-                                  partials, dtot, c->stream);
+                                  partials, slot.p ? slot.p : dtot, c->stream);
     if (e != hipSuccess) return fail_hip(e, "moments kernel launch");
     if (!totals) return LBM_OK;
-    double h[kPartials];
-    e = hipMemcpyAsync(h, dtot, sizeof h, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    if (slot.p) {
+        e = slot.wait(c->stream);
+        if (e == hipSuccess) std::memcpy(h, slot.p, sizeof h);
+    } else {
+        e = hipMemcpyAsync(h, dtot, sizeof h, hipMemcpyDeviceToHost, c->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    }
     if (e != hipSuccess) return fail_hip(e, "moments read-back");
     // sum over fluid cells of rho = (fluid cells) rho0 + sum (rho - rho0); the device sums
     // the deviations and counts the fluid cells
@@ -689,7 +749,10 @@ int lbm_grad(lbm_ctx *c, const lbm_grad_spec *spec, void *workspace, double *obj
     }
     // seed the reverse sweep with dJ/df at the final state
     void *lam_in = ws + l.lam_a, *lam_out = ws + l.lam_b;
-    double *gpart = (double *)(ws + l.gpart), *jpart = (double *)(ws + l.jpart), *sums = (double *)(ws + l.sums);
+    double h[1 + kGradPartialsHost];
+    HostSlot slot(sizeof h);
+    double *gpart = (double *)(ws + l.gpart), *jpart = (double *)(ws + l.jpart);
+    double *sums = slot.p ? slot.p : (double *)(ws + l.sums);
     e = launch_seed(c->p.lattice, c->p.storage, c->grid, c->k64, c->k32, c->pop[c->cur], lam_in, jpart,
                     spec->objective, (int)spec->outlet_plane, c->links, st);
     if (e == hipSuccess) e = launch_sum(jpart, nb, 1, sums, st);
@@ -711,10 +774,10 @@ int lbm_grad(lbm_ctx *c, const lbm_grad_spec *spec, void *workspace, double *obj
         }
     }
     e = launch_sum(gpart, na, kGradPartialsHost, sums + 1, st);
-    double h[1 + kGradPartialsHost];
-    if (e == hipSuccess) e = hipMemcpyAsync(h, sums, sizeof h, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e == hipSuccess && !slot.p) e = hipMemcpyAsync(h, sums, sizeof h, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = slot.wait(st);
     if (e != hipSuccess) return fail_hip(e, "gradient read-back");
+    if (slot.p) std::memcpy(h, slot.p, sizeof h);
     *objective = h[0];
     if (dtau) *dtau = h[7];
     if (dtensor) {
@@ -773,12 +836,14 @@ int lbm_objective(lbm_ctx *c, int32_t objective, int64_t outlet_plane, double *v
                     (long long)(c->p.nx - 1));
     // the moments partials hold one double per seed work-group, the totals slot the sum
     double *jpart = c->partials;
-    double *sum = c->partials + kPartials * (size_t)moments_groups(c->grid);
+    HostSlot slot(sizeof(double));
+    double *sum = slot.p ? slot.p : c->partials + kPartials * (size_t)moments_groups(c->grid);
     hipError_t e = launch_seed(c->p.lattice, c->p.storage, c->grid, c->k64, c->k32, c->pop[c->cur], nullptr, jpart,
                                objective, (int)outlet_plane, c->links, c->stream);
     if (e == hipSuccess) e = launch_sum(jpart, moments_groups(c->grid), 1, sum, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(value, sum, sizeof(double), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    if (e == hipSuccess && !slot.p) e = hipMemcpyAsync(value, sum, sizeof(double), hipMemcpyDeviceToHost, c->stream);
+    if (e == hipSuccess) e = slot.wait(c->stream);
+    if (e == hipSuccess && slot.p) *value = *slot.p;
     return e == hipSuccess ? LBM_OK : fail_hip(e, "objective evaluation");
 }
 

@@ -69,5 +69,5 @@ extern "C" int lbm_moments_static(lbm_ctx *c, double *rho, double *s, double *to
     e = scratch_on(device, &base);
     if (e != hipSuccess) return fail_hip(e, "address of the static scratch array");
     double *partials = (double *)base;
-    return moments_with(c, rho, s, totals, partials, partials + kPartials * (size_t)groups);
+    return moments_with(c, rho, s, totals, partials, partials + kPartials * (size_t)groups, false);
 }
