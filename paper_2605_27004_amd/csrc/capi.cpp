@@ -342,8 +342,26 @@ template <typename C> StepConsts<C> consts_for(const lbm_params &p, const Prepar
     return k;
 }
 
-// Scratch layout: [link words, 4 bytes per cell, when masked][partials][totals], 256-byte
-// aligned pieces.
+// Whether a masked grid stores its rows compact (RowRec). The index fits in the link words' share of the
+// scratch: 8 ceil(nx / 30) + 4 + 2 nx bytes for a row, against 4 nx. Us per step, link words -> compact
+// rows; ellipsoids that leave 60% fluid, and two plates with fluid between:
+//  * FP64, any size: D3Q19 128^3 102.5 -> 78.0 and 108.0 -> 105.9, 256 x 128 x 128 201 -> 140 and 213.6 ->
+//    209.4, D3Q27 64^3 22.5 -> 20.2 and 23.2 -> 22.9, 128 x 8 x 8 6.5 -> 6.3 and 6.3 -> 6.1. Random
+//    single cells gain nothing until they are many (D3Q19 128^3 with 5% solid 110.8 -> 113.3).
+//  * FP32 from 64 MB on and rows of 128 cells: D3Q27 256^3 588 -> 440 and 588 -> 590, 512^3 4,807 -> 3,401,
+//    D3Q19 128^3 54 -> 51 and 53.9 -> 52.6, 512 x 128 x 128 210 -> 162 and 211 -> 203, 128 x 64 x 64 16.9 ->
+//    16.6; a row index, read before anything else can start, costs more on smaller grids: 128 x 32 x 32
+//    5.5 -> 6.4, 64^3 10.0 -> 10.4 and 8.8 -> 10.2.
+//  * Never for 16-bit storage, where the lookups cost as much as the solid cells' bytes: D3Q27 FP16 256^3
+//    319 -> 304 and 324 -> 329, but 384 -> 471 with 10% random single cells.
+bool compact_rows(const lbm_params &p, int q, int bytes, uint32_t n)
+{
+    if (p.lattice == LBM_D2Q9 || p.nx % 64 != 0 || p.nx > (int64_t)kMaxCompactRow) return false;
+    return bytes == 8 || (bytes == 4 && p.nx >= 128 && 2.0 * q * bytes * n >= 64e6);
+}
+
+// Scratch layout: [link words or row index, 4 bytes per cell, when masked][partials][totals],
+// 256-byte aligned pieces.
 int64_t links_bytes(const lbm_params &p, uint32_t n)
 {
     return (p.flags & (LBM_FLAG_MASK | LBM_FLAG_GRAY)) ? ((int64_t)n * 4 + 255) / 256 * 256 : 0;
@@ -497,6 +515,7 @@ int lbm_init(lbm_ctx **out, const lbm_params *p, void *pop_a, void *pop_b, void 
     c->pop[1] = pop_b;
     c->cur = 0;
     c->links = masked ? (uint32_t *)scratch : nullptr;
+    if (masked && compact_rows(*p, pr.q, pr.bytes, pr.n)) c->grid.nrec = ((uint32_t)p->nx + kRecCells - 1u) / kRecCells;
     c->gray = grayed ? (float *)scratch : nullptr;
     c->partials = (double *)((char *)scratch + links_bytes(*p, pr.n));
     c->stream = (hipStream_t)stream;

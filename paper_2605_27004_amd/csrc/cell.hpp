@@ -642,6 +642,136 @@ template <typename S> __device__ inline void slot_at(S *base, const Grid &g, con
     }
 }
 
+// ---- compact rows ----------------------------------------------------------------------------
+//
+// A cell of a grid of compact rows (RowRec), with the records of the nine rows around it. y and z are the
+// same for the whole wave.
+struct RowCell {
+    uint32_t own;         // canonical index
+    uint32_t place;       // its place in its row: the number of fluid cells before it
+    uint32_t row;         // storage index of the row's first cell within the z-plane
+    AxisOff oy;
+    uint64_t z0, zm, zp;
+    uint32_t bit;         // its bit in the records
+    bool first, last;     // the first / last cell of the row
+    RowRec rec[3][3];     // [dz + 1][dy + 1]
+    uint32_t count[3][3];
+};
+
+// The rows around the row (y, z), and their fluid cells.
+struct Rows {
+    uint32_t at[3][3];
+    uint32_t count[3][3];
+};
+__device__ inline Rows rows_of(const Grid &g, const RowIndex &ix, int32_t y, int32_t z)
+{
+    Rows r;
+    const uint32_t yu = (uint32_t)__builtin_amdgcn_readfirstlane(y), zu = (uint32_t)__builtin_amdgcn_readfirstlane(z);
+    const uint32_t ny = (uint32_t)g.ny, nz = (uint32_t)g.nz;
+    const uint32_t zs[3] = {zu == 0u ? nz - 1u : zu - 1u, zu, zu == nz - 1u ? 0u : zu + 1u};
+    const uint32_t ys[3] = {yu == 0u ? ny - 1u : yu - 1u, yu, yu == ny - 1u ? 0u : yu + 1u};
+#pragma unroll
+    for (int dz = 0; dz < 3; ++dz)
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy) {
+            r.at[dz][dy] = zs[dz] * ny + ys[dy];
+            r.count[dz][dy] = ix.count[r.at[dz][dy]];
+        }
+    return r;
+}
+
+// The cell of the given code (row_code) in the middle one of the rows.
+__device__ inline RowCell row_cell(const Grid &g, const RowIndex &ix, const Rows &rows, uint32_t code, int32_t y, int32_t z)
+{
+    RowCell c;
+    const uint32_t q = code >> 5;
+    c.bit = code & 31u;
+    const uint32_t x = q * kRecCells + c.bit - 1u;
+    c.own = rows.at[1][1] * (uint32_t)g.nx + x;
+    const int32_t yu = __builtin_amdgcn_readfirstlane(y), zu = __builtin_amdgcn_readfirstlane(z);
+    c.row = row_off(g, (uint32_t)yu, c.oy);
+    c.z0 = (uint64_t)zu * g.zs;
+    c.zm = (uint64_t)(zu == 0 ? g.nz - 1 : zu - 1) * g.zs;
+    c.zp = (uint64_t)(zu == g.nz - 1 ? 0 : zu + 1) * g.zs;
+    c.first = x == 0u;
+    c.last = x == (uint32_t)g.nx - 1u;
+#pragma unroll
+    for (int dz = 0; dz < 3; ++dz)
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy) {
+            // (a scalar base and a 32-bit byte offset)
+            c.rec[dz][dy] = *reinterpret_cast<const RowRec *>(
+                reinterpret_cast<const char *>(ix.rec + (uint64_t)rows.at[dz][dy] * g.nrec) + q * (uint32_t)sizeof(RowRec));
+            c.count[dz][dy] = rows.count[dz][dy];
+        }
+    c.place = c.rec[1][1].before + (uint32_t)__popc(c.rec[1][1].fluid & ((1u << c.bit) - 2u));
+    return c;
+}
+
+// Whether the cell at distance sx along x, in the row that direction (., cy, cz) pulls from, is fluid.
+__device__ inline bool fluid_from(const RowCell &c, int sx, int cy, int cz)
+{
+    return (c.rec[1 - cz][1 - cy].fluid & (1u << c.bit) << 1 >> (1 - sx)) != 0u;
+}
+
+// The place of that cell in its row (any number if it is solid).
+__device__ inline uint32_t place_from(const RowCell &c, int sx, int cy, int cz)
+{
+    const RowRec &r = c.rec[1 - cz][1 - cy];
+    const uint32_t n = r.before + (uint32_t)__popc(r.fluid & ((1u << c.bit) - 2u));
+    if (sx < 0) return c.first ? c.count[1 - cz][1 - cy] - 1u : n - 1u;
+    if (sx > 0) return c.last ? 0u : n + (r.fluid >> c.bit & 1u);
+    return n;
+}
+
+__device__ inline Ref own_ref(const RowCell &c) { return Ref{c.z0, c.row + c.place}; }
+
+__device__ inline Ref nbr(const RowCell &c, int cx, int cy, int cz)
+{
+    return Ref{cz > 0 ? c.zm : (cz < 0 ? c.zp : c.z0), c.row + back(c.oy, cy) + place_from(c, -cx, cy, cz)};
+}
+
+__device__ inline bool same_z(const RowCell &, int cz) { return cz == 0; }
+
+template <int LAT> __device__ inline Slot slot_plus(const RowCell &c, int p, uint32_t)
+{
+    const PairRow v = Lattice<LAT>::pair(p);
+    return Slot{!fluid_from(c, -v.cx, v.cy, v.cz), v.cz == 0, 2 * p + 2, 2 * p + 1, own_ref(c), src_plus<LAT>(c, p)};
+}
+
+template <int LAT> __device__ inline Slot slot_minus(const RowCell &c, int p, uint32_t)
+{
+    const PairRow v = Lattice<LAT>::pair(p);
+    return Slot{!fluid_from(c, v.cx, -v.cy, -v.cz), v.cz == 0, 2 * p + 1, 2 * p + 2, own_ref(c), src_minus<LAT>(c, p)};
+}
+
+// The cell (x, y, z) and its link word (bit 0: it is solid), for both kinds of masked grid: ROWS for
+// compact rows, else link words or no mask (links null).
+template <bool ROWS> __device__ inline auto walled_cell(const Grid &g, const uint32_t *links, int32_t x, int32_t y, int32_t z)
+{
+    if constexpr (ROWS) {
+        const RowIndex ix = row_index(g, links);
+        return row_cell(g, ix, rows_of(g, ix, y, z), row_code((uint32_t)x), y, z);
+    } else {
+        return cell_of(g, x, y, z);
+    }
+}
+__device__ inline uint32_t link_word(const Cell &c, const uint32_t *links) { return links ? links[c.own] : 0u; }
+__device__ inline uint32_t link_word(const RowCell &c, const uint32_t *) { return fluid_from(c, 0, 0, 0) ? 0u : 1u; }
+
+// Whether a cell has a place of its own (a solid cell of a compact row has none).
+__device__ inline bool has_place(const RowCell &c) { return fluid_from(c, 0, 0, 0); }
+__device__ inline bool has_place(const Cell &) { return true; }
+
+// A slot's value with 32-bit byte offsets from the start of the populations (below 4 GiB): one select,
+// where slot_at selects between two 64-bit bases.
+template <typename S> __device__ inline S ld_slot_narrow(const S *base, const Grid &g, const Slot &s)
+{
+    const uint32_t own = ((uint32_t)s.own.zo + (uint32_t)s.own_plane * g.bc + s.own.idx) * (uint32_t)sizeof(S);
+    const uint32_t from = ((uint32_t)s.src.zo + (uint32_t)s.src_plane * g.bc + s.src.idx) * (uint32_t)sizeof(S);
+    return *reinterpret_cast<const S *>(reinterpret_cast<const char *>(base) + (uint64_t)(s.bounce ? own : from));
+}
+
 template <typename S> __device__ inline S ld_slot(const S *base, const Grid &g, const Slot &s)
 {
     const S *p;

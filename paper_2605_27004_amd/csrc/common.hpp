@@ -58,13 +58,49 @@ struct Grid {
     uint32_t bq;    // q bc: elements per block
     uint32_t zs;    // q nx ny: elements per z-plane (the bytes of one z-plane stay below 4 GiB)
     uint32_t lb;    // batched domains only: log2 of the cells per linear block (bc = 2^lb)
+    uint32_t nrec;  // masked grids of compact rows only: records per row; else 0 (see RowRec)
 };
+
+// Compact rows. In a masked three-dimensional grid whose rows are a multiple of 64 cells, each row
+// stores its fluid cells first, in the order of x; everything else about the layout stays (a row
+// begins where it did). Solid cells are neither read nor written, and a wave of the step works on 64
+// fluid cells. In the place of the link words (4 bytes per cell) the scratch then holds, for the
+// ny nz rows in order,
+//   RowRec[nrec] per row   which cells are fluid, and how many fluid cells come before them,
+//   uint32 per row         the row's fluid cells,
+//   uint16[nx] per row     the x of the row's fluid cells as row_code(x), then row_code(0).
+// A record is for 30 cells, and holds the cell before and the cell after them as well (periodic), so
+// that a cell's record alone says all about itself and its two neighbours in the row.
+struct RowRec {
+    uint32_t fluid;   // bit 1 + j: cell 30 q + j of the row is fluid; bit 0: the cell before; the bit after
+                      // the last cell: the cell after
+    uint32_t before;  // fluid cells of the row before cell 30 q
+};
+constexpr uint32_t kRecCells = 30u;
+constexpr uint32_t kMaxCompactRow = 2048u * kRecCells;  // row_code fits 16 bits
+__host__ __device__ inline uint32_t row_code(uint32_t x) { return x / kRecCells << 5 | (x % kRecCells + 1u); }
+
+// The three arrays.
+struct RowIndex {
+    const RowRec *rec;
+    const uint32_t *count;
+    const uint16_t *code;
+};
+__host__ __device__ inline RowIndex row_index(const Grid &g, const uint32_t *scratch)
+{
+    const uint64_t rows = (uint64_t)(uint32_t)g.ny * (uint32_t)g.nz;
+    RowIndex r;
+    r.rec = reinterpret_cast<const RowRec *>(scratch);
+    r.count = reinterpret_cast<const uint32_t *>(r.rec + rows * g.nrec);
+    r.code = reinterpret_cast<const uint16_t *>(r.count + rows);
+    return r;
+}
 
 // ---- launchers (kernels.hip) -----------------------------------------------------------
 // All return hipSuccess or the launch error; they enqueue on `stream` and never synchronise.
 
-// links: per-cell link words (bit 0: the cell is solid; bit i: the cell x - c_i is solid) or
-// null for a grid without solid cells.
+// links: per-cell link words (bit 0: the cell is solid; bit i: the cell x - c_i is solid), the row
+// index of a grid of compact rows (g.nrec != 0), or null for a grid without solid cells.
 hipError_t launch_links(int lattice, const Grid &g, const uint8_t *mask, uint32_t *links, hipStream_t stream);
 
 hipError_t launch_init(int lattice, int storage, int order, const Grid &g, const StepConsts<double> &k,

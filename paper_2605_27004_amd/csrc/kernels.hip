@@ -92,8 +92,9 @@ enum StepMode : int { kPlain = 0, kLinks = 1, kGray = 2, kStream = 3 };
 // How the step kernel pulls (launch_step picks): every population with its own shifted load, in
 // work-groups that are boxes of block_x x block_y cells (kPullShifted) or runs of 256 consecutive
 // cells of a z-plane (kPullFlat); or the lane exchange inside whole rows (kPullRows: pull_aligned, or
-// pull_rows_lds for FP16 storage).
-enum PullKind : int { kPullShifted = 0, kPullRows = 1, kPullFlat = 2 };
+// pull_rows_lds for FP16 storage). kPullCompact: the links step over compact rows
+// (RowRec), where x counts a row's fluid cells; kPullCompactWide: the same for populations of 4 GiB and more.
+enum PullKind : int { kPullShifted = 0, kPullRows = 1, kPullFlat = 2, kPullCompact = 3, kPullCompactWide = 4 };
 
 template <int LAT, typename S, int PULL>
 __device__ inline void pull_aligned(const S *__restrict__ src, const Grid &g, const Cell &c, int32_t x, bool live,
@@ -225,6 +226,7 @@ __global__ __launch_bounds__(256) void k_step(const S *__restrict__ src, S *__re
                                               const uint32_t *__restrict__ links, const float *__restrict__ gray)
 {
     constexpr bool GENERAL = MODE == kLinks;
+    constexpr bool COMPACT = PULL == kPullCompact || PULL == kPullCompactWide;
     constexpr bool ALIGNED = PULL == kPullRows;
     static_assert(!(ALIGNED && GENERAL), "the lane-exchange pull serves the periodic, gray and streaming steps");
     using L = Lattice<LAT>;
@@ -244,6 +246,7 @@ __global__ __launch_bounds__(256) void k_step(const S *__restrict__ src, S *__re
 
     C gp[NP + 1], gm[NP + 1];
     Cell c;
+    Ref own;
     if constexpr (ALIGNED) {
         const bool live = y < g.ny;
         c = cell_of(g, x, live ? y : 0, z);
@@ -255,6 +258,60 @@ __global__ __launch_bounds__(256) void k_step(const S *__restrict__ src, S *__re
         else
             pull_aligned<LAT, S, PULL>(src, g, c, x, live, gp, gm);
         if (!live) return;
+        own = own_ref(c);
+    } else if constexpr (COMPACT) {
+        if (x >= g.nx || y >= g.ny) return;
+        const RowIndex ix = row_index(g, links);
+        const uint32_t row = (uint32_t)__builtin_amdgcn_readfirstlane(z * g.ny + y);
+        {
+            // which 64 cells: turned by a number that changes with the row, because the waves past the
+            // fluid cells, which have nothing to do, would all lie on the same SIMDs or shader engines
+            // otherwise (D3Q27 FP32 256^3, 60% fluid, 618 -> 438 us)
+            const uint32_t chunks = (uint32_t)g.nx >> 6, ch = (uint32_t)__builtin_amdgcn_readfirstlane(x >> 6);
+            x = (int32_t)((ch + (row * 0x9E3779B1u >> 12)) % chunks << 6 | ((uint32_t)x & 63u));
+        }
+        const Rows rows = rows_of(g, ix, y, z);
+        // lanes past the row's fluid cells but in its last cache line store what they compute, so
+        // that the line is whole; nothing reads it
+        constexpr uint32_t line = 128u / (uint32_t)sizeof(S);
+        if ((uint32_t)x >= (rows.count[1][1] + line - 1u) / line * line) return;
+        uint32_t fluid = 0u;
+#pragma unroll
+        for (int r = 0; r < 9; ++r) fluid += rows.count[r / 3][r % 3] == (uint32_t)g.nx ? 1u : 0u;
+        if (fluid == 9u) {
+            // nine rows without a solid cell: plain pulls
+            c = cell_of(g, x, y, z);
+#pragma unroll
+            for (int j = 0; j < L::Q; ++j) {
+                const int i = kPull.dir[j], p = (i - 1) / 2;
+                if (i == 0)
+                    gp[0] = Conv<S>::ld(ld_pop(src, g, 0, own_ref(c)));
+                else if (i & 1)
+                    gp[p + 1] = Conv<S>::ld(ld_pop(src, g, i, src_plus<LAT>(c, p)));
+                else
+                    gm[p + 1] = Conv<S>::ld(ld_pop(src, g, i, src_minus<LAT>(c, p)));
+            }
+            own = own_ref(c);
+        } else {
+            RowCell rc = row_cell(g, ix, rows, (ix.code + (uint64_t)row * (uint32_t)g.nx)[x], y, z);
+            rc.place = (uint32_t)x;
+            auto pull = [&](const Slot &sl) {
+                if constexpr (PULL == kPullCompact) return ld_slot_narrow(src, g, sl);
+                else return ld_slot(src, g, sl);
+            };
+#pragma unroll
+            for (int j = 0; j < L::Q; ++j) {
+                const int i = kPull.dir[j], p = (i - 1) / 2;
+                if (i == 0)
+                    gp[0] = Conv<S>::ld(ld_pop(src, g, 0, own_ref(rc)));
+                else if (i & 1)
+                    gp[p + 1] = Conv<S>::ld(pull(slot_plus<LAT>(rc, p, 0u)));
+                else
+                    gm[p + 1] = Conv<S>::ld(pull(slot_minus<LAT>(rc, p, 0u)));
+            }
+            own = own_ref(rc);
+        }
+        collide_cell<LAT, ORDER, true, C, kClose<S>>(k, gp, gm);
     } else if constexpr (GENERAL) {
         if (x >= g.nx || y >= g.ny) return;
         c = cell_of(g, x, y, z);
@@ -278,9 +335,11 @@ __global__ __launch_bounds__(256) void k_step(const S *__restrict__ src, S *__re
             }
             collide_cell<LAT, ORDER, true, C, kClose<S>>(k, gp, gm);
         }
+        own = own_ref(c);
     } else {
         if (x >= g.nx || y >= g.ny) return;
         c = cell_of(g, x, y, z);
+        own = own_ref(c);
 #pragma unroll
         for (int j = 0; j < L::Q; ++j) {
             const int i = kPull.dir[j], p = (i - 1) / 2;
@@ -312,7 +371,7 @@ __global__ __launch_bounds__(256) void k_step(const S *__restrict__ src, S *__re
             gm[p + 1] = fmad(mg, pp[p + 1] - gm[p + 1], gm[p + 1]);
         }
     }
-    const PlaneStores ps = plane_stores(dst, g, own_ref(c));
+    const PlaneStores ps = plane_stores(dst, g, own);
     st_plane_aux<AUX>(ps, 0, Conv<S>::st(gp[0]));
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
@@ -341,9 +400,53 @@ __global__ __launch_bounds__(256) void k_links(const uint8_t *__restrict__ mask,
     links[c.own] = w;
 }
 
+// The row index (RowRec) from a uint8 solid mask: one wave per row.
+__global__ __launch_bounds__(256) void k_row_index(const uint8_t *__restrict__ mask, RowRec *__restrict__ rec,
+                                                   uint32_t *__restrict__ count, uint16_t *__restrict__ code, const Grid g)
+{
+    const uint32_t row = blockIdx.x * 4u + (threadIdx.x >> 6), lane = threadIdx.x & 63u;
+    if (row >= (uint32_t)g.ny * (uint32_t)g.nz) return;
+    const uint32_t nx = (uint32_t)g.nx;
+    const uint8_t *m = mask + (uint64_t)row * nx;
+    // the records, 64 at a time
+    uint32_t before = 0u;
+    for (uint32_t q0 = 0u; q0 < g.nrec; q0 += 64u) {
+        const uint32_t q = q0 + lane;
+        RowRec r{0u, 0u};
+        uint32_t cells = 0u;
+        if (q < g.nrec) {
+            const uint32_t x0 = q * kRecCells;
+            const uint32_t n = x0 + kRecCells <= nx ? kRecCells : nx - x0;
+            for (uint32_t b = 0u; b < n + 2u; ++b) {
+                const uint32_t x = b == 0u ? (x0 == 0u ? nx - 1u : x0 - 1u) : (x0 + b - 1u == nx ? 0u : x0 + b - 1u);
+                if (m[x] == 0) r.fluid |= 1u << b;
+            }
+            cells = (uint32_t)__popc(r.fluid & ((1u << (n + 1u)) - 2u));
+        }
+        uint32_t upto = cells;
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t o = __shfl_up(upto, d);
+            if (lane >= (uint32_t)d) upto += o;
+        }
+        r.before = before + upto - cells;
+        if (q < g.nrec) rec[(uint64_t)row * g.nrec + q] = r;
+        before += __shfl(upto, 63);
+    }
+    if (lane == 0u) count[row] = before;
+    // the fluid cells' x
+    uint32_t at = 0u;
+    for (uint32_t x = lane; x < nx; x += 64u) {  // (nx is a multiple of 64: all lanes take part)
+        const uint64_t b = __ballot(m[x] == 0);
+        if (m[x] == 0)
+            code[(uint64_t)row * nx + at + (uint32_t)__popcll(b & ((1ull << lane) - 1ull))] = (uint16_t)row_code(x);
+        at += (uint32_t)__popcll(b);
+    }
+    for (uint32_t x = at + lane; x < nx; x += 64u) code[(uint64_t)row * nx + x] = (uint16_t)row_code(0u);
+}
+
 // f_i(0, x) = f^eq_i(rho(x), s(x)) in FP64, stored as a deviation in the slot the canonical
 // gather reads for direction i at x (solid cells are skipped).
-template <int LAT, typename S, int ORDER>
+template <int LAT, typename S, int ORDER, bool ROWS>
 __global__ __launch_bounds__(256) void k_init(const double *__restrict__ rho_in, const double *__restrict__ s_in,
                                               const uint32_t *__restrict__ links, S *__restrict__ dst,
                                               const Grid g, const StepConsts<double> k)
@@ -355,10 +458,11 @@ __global__ __launch_bounds__(256) void k_init(const double *__restrict__ rho_in,
     const int32_t y = blockIdx.y * blockDim.y + threadIdx.y;
     const int32_t z = blockIdx.z;
     if (x >= g.nx || y >= g.ny) return;
-    const Cell c = cell_of(g, x, y, z);
-    const uint32_t lk = links ? links[c.own] : 0u;
+    const auto c = walled_cell<ROWS>(g, links, x, y, z);
+    const uint32_t lk = link_word(c, links);
     if (lk & 1u) {  // solid: no state; its own slots are set to zero like every step does
-        for (int i = 0; i < L::Q; ++i) st_pop(dst, g, i, own_ref(c), Conv<S>::st(C(0)));
+        if (has_place(c))
+            for (int i = 0; i < L::Q; ++i) st_pop(dst, g, i, own_ref(c), Conv<S>::st(C(0)));
         return;
     }
     const double rho = rho_in[c.own];
@@ -384,7 +488,7 @@ constexpr int kRedThreads = 256;
 // w, w + G, w + 2G, ... of the row_grid order, each lane sums its cells in that order, and the
 // work-group adds its lanes in a fixed tree, so the totals are reproducible bit for bit and
 // the partials need a small scratch of constant size.
-template <int LAT, typename S>
+template <int LAT, typename S, bool ROWS>
 __global__ __launch_bounds__(kRedThreads) void k_moments(const S *__restrict__ src, const uint32_t *__restrict__ links,
                                                          double *__restrict__ rho_out, double *__restrict__ s_out,
                                                          double *__restrict__ partials, const Grid g,
@@ -402,8 +506,8 @@ __global__ __launch_bounds__(kRedThreads) void k_moments(const S *__restrict__ s
         const int32_t y = (int32_t)(((t / tiles_x) % tiles_y) * blockDim.y + threadIdx.y);
         const int32_t z = (int32_t)(t / (tiles_x * tiles_y));
         if (x >= g.nx || y >= g.ny) continue;
-        const Cell c = cell_of(g, x, y, z);
-        const uint32_t lk = links ? links[c.own] : 0u;
+        const auto c = walled_cell<ROWS>(g, links, x, y, z);
+        const uint32_t lk = link_word(c, links);
         double rho = 0.0, ux = 0.0, uy = 0.0, uz = 0.0;
         if (!(lk & 1u)) {
             double gp[NP + 1], gm[NP + 1];
@@ -463,7 +567,7 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_partials(const double *_
 }
 
 // Canonical-order permutations of the state (see the file header and Slot).
-template <int LAT, typename S, int MODE>
+template <int LAT, typename S, int MODE, bool ROWS>
 __global__ __launch_bounds__(256) void k_permute(const void *__restrict__ in, void *__restrict__ out,
                                                  const uint32_t *__restrict__ links, const Grid g,
                                                  const StepConsts<double> k)
@@ -474,8 +578,8 @@ __global__ __launch_bounds__(256) void k_permute(const void *__restrict__ in, vo
     const int32_t y = blockIdx.y * blockDim.y + threadIdx.y;
     const int32_t z = blockIdx.z;
     if (x >= g.nx || y >= g.ny) return;
-    const Cell c = cell_of(g, x, y, z);
-    const uint32_t lk = links ? links[c.own] : 0u;
+    const auto c = walled_cell<ROWS>(g, links, x, y, z);
+    const uint32_t lk = link_word(c, links);
     const bool solid = lk & 1u;
     auto move = [&](int i, Slot sl, double sigma) {
         if constexpr (MODE == 0) {
@@ -753,7 +857,7 @@ constexpr int kGradPartials = 7;  // symmetric G (6) and d tau, per work-group
 // work-group. kind 0: flux through the plane x = plane_x, J = sum (j_x + F_x/2); kind 1: kinetic
 // energy, J = sum |j + F/2|^2 / (2 rho). Like k_moments, the launch has a fixed number of
 // work-groups that stride over the row tiles in a fixed order (reproducible sums).
-template <int LAT, typename S>
+template <int LAT, typename S, bool ROWS>
 __global__ __launch_bounds__(256) void k_seed(const S *__restrict__ src, typename Conv<S>::C *__restrict__ lam,
                                               double *__restrict__ jpart, const Grid g,
                                               const StepConsts<typename Conv<S>::C> k, const int kind, const int plane_x,
@@ -772,8 +876,8 @@ __global__ __launch_bounds__(256) void k_seed(const S *__restrict__ src, typenam
         const int32_t y = (int32_t)(((t / tiles_x) % tiles_y) * blockDim.y + threadIdx.y);
         const int32_t z = (int32_t)(t / (tiles_x * tiles_y));
         if (x >= g.nx || y >= g.ny) continue;
-        const Cell c = cell_of(g, x, y, z);
-        const uint32_t lk = links ? links[c.own] : 0u;
+        const auto c = walled_cell<ROWS>(g, links, x, y, z);
+        const uint32_t lk = link_word(c, links);
         C gp[NP + 1], gm[NP + 1];
         gp[0] = Conv<S>::ld(ld_pop(src, g, 0, own_ref(c)));
 #pragma unroll
@@ -801,7 +905,7 @@ __global__ __launch_bounds__(256) void k_seed(const S *__restrict__ src, typenam
             base = C(-0.5) * fmad(ux, ux, fmad(uy, uy, uz * uz));
             jv += 0.5 * ((double)mx * mx + (double)my * my + (double)mz * mz) / (double)rho;
         }
-        if (lam) {
+        if (lam && has_place(c)) {
             // lam_i = base + u . c_i
             st_pop(lam, g, 0, own_ref(c), base);
 #pragma unroll
@@ -838,11 +942,41 @@ template <int LAT> __device__ inline Slot adjoint_slot_minus(const Cell &c, int 
     return Slot{bounce, same_z(c, Lattice<LAT>::pair(p).cz), 2 * p + 1, 2 * p + 2, own_ref(c), src_plus<LAT>(c, p)};
 }
 
+template <int LAT> __device__ inline Slot adjoint_slot_plus(const RowCell &c, int p, uint32_t)
+{
+    const PairRow v = Lattice<LAT>::pair(p);
+    return Slot{!fluid_from(c, v.cx, -v.cy, -v.cz), v.cz == 0, 2 * p + 2, 2 * p + 1, own_ref(c), src_minus<LAT>(c, p)};
+}
+
+template <int LAT> __device__ inline Slot adjoint_slot_minus(const RowCell &c, int p, uint32_t)
+{
+    const PairRow v = Lattice<LAT>::pair(p);
+    return Slot{!fluid_from(c, -v.cx, v.cy, v.cz), v.cz == 0, 2 * p + 1, 2 * p + 2, own_ref(c), src_plus<LAT>(c, p)};
+}
+
+// Solid cells of an adjoint launch: none, marked by link words, or by row records (compact rows).
+enum AdjointWalls : int { kNoWalls = 0, kLinkWords = 1, kCompactRows = 2 };
+
+// The cell of a lane: (x, y, z), or in compact rows the x-th fluid cell of the row (y, z).
+template <int WALLS>
+__device__ inline auto adjoint_at(const Grid &g, const uint32_t *links, int32_t x, int32_t y, int32_t z)
+{
+    if constexpr (WALLS == kCompactRows) {
+        const RowIndex ix = row_index(g, links);
+        const uint32_t row = (uint32_t)__builtin_amdgcn_readfirstlane(z * g.ny + y);
+        RowCell c = row_cell(g, ix, rows_of(g, ix, y, z), (ix.code + (uint64_t)row * (uint32_t)g.nx)[x], y, z);
+        c.place = (uint32_t)x;
+        return c;
+    } else {
+        return cell_of(g, x, y, z);
+    }
+}
+
 // One reverse step at one cell: lam_in = lam(t+1) (canonical), state = the buffer whose gather
 // gives f(t); writes lam(t) at the cell, adds d m to dmask and the cell's G / d tau to G, dtau.
-// LINKS = false compiles the grid without solid cells (links is null): every slot is then a
+// WALLS = kNoWalls compiles the grid without solid cells (links is null): every slot is then a
 // plain pull and the bounce-back selections drop out of the code.
-template <int LAT, typename S, int ORDER, bool FORCED, bool LINKS>
+template <int LAT, typename S, int ORDER, bool FORCED, int WALLS>
 __device__ inline void adjoint_cell(const S *__restrict__ state, const typename Conv<S>::C *__restrict__ lam_in,
                                     typename Conv<S>::C *__restrict__ lam_out, const float *__restrict__ gray,
                                     const uint32_t *__restrict__ links, double *__restrict__ dmask, const Grid &g,
@@ -853,13 +987,22 @@ __device__ inline void adjoint_cell(const S *__restrict__ state, const typename 
     using C = typename Conv<S>::C;
     constexpr int NP = L::NP;
     const bool inside = x < g.nx && y < g.ny;
-    const Cell c = cell_of(g, inside ? x : 0, inside ? y : 0, z);
-    const uint32_t lk = (LINKS && inside && links) ? links[c.own] : 0u;
+    // (in compact rows x counts the row's fluid cells)
+    const auto c = adjoint_at<WALLS>(g, links, inside ? x : 0, inside ? y : 0, z);
+    uint32_t lk = 0u;
+    if constexpr (WALLS == kLinkWords) lk = (inside && links) ? links[c.own] : 0u;
+    if constexpr (WALLS == kCompactRows) lk = (uint32_t)x >= c.count[1][1] ? 1u : 0u;
     const PlaneStores out = plane_stores(lam_out, g, own_ref(c));
-    if (LINKS && inside && (lk & 1u)) {
-        // a solid cell holds no state: its adjoint is zero and it adds no sensitivity
+    if (WALLS != kNoWalls && inside && (lk & 1u)) {
+        // a solid cell holds no state: its adjoint is zero and it adds no sensitivity (in compact rows:
+        // what is left of the row's last cache line)
+        constexpr uint32_t line = 128u / (uint32_t)sizeof(C);
+        bool store = true;
+        if constexpr (WALLS == kCompactRows) store = (uint32_t)x < (c.count[1][1] + line - 1u) / line * line;
+        if (store) {
 #pragma unroll
-        for (int i = 0; i < L::Q; ++i) st_plane(out, i, C(0));
+            for (int i = 0; i < L::Q; ++i) st_plane(out, i, C(0));
+        }
     } else if (inside) {
         // forward quantities at x (the canonical gather, bounce-back slots included)
         C gp[NP + 1], gm[NP + 1];
@@ -961,7 +1104,7 @@ __device__ inline void adjoint_cell(const S *__restrict__ state, const typename 
 // of several row tiles, carrying per-lane FP64 sums across the rows, measured slower at 128^3:
 // 95 us per step for one row against 107.5 (2 rows), 109 (4) and 112 (11) with the sums in
 // registers (138 VGPRs), and 103 (2 rows) with the sums in LDS.
-template <int LAT, typename S, int ORDER, bool FORCED, bool LINKS>
+template <int LAT, typename S, int ORDER, bool FORCED, int WALLS>
 __global__ __launch_bounds__(256) void k_adjoint(const S *__restrict__ state, const typename Conv<S>::C *__restrict__ lam_in,
                                                  typename Conv<S>::C *__restrict__ lam_out,
                                                  const float *__restrict__ gray, const uint32_t *__restrict__ links,
@@ -977,7 +1120,7 @@ __global__ __launch_bounds__(256) void k_adjoint(const S *__restrict__ state, co
     const int32_t z = (int32_t)(f / tiles_y);
     C G[6] = {C(0), C(0), C(0), C(0), C(0), C(0)};
     C dtau = C(0);
-    adjoint_cell<LAT, S, ORDER, FORCED, LINKS>(state, lam_in, lam_out, gray, links, dmask, g, k, x, y, z, G, dtau);
+    adjoint_cell<LAT, S, ORDER, FORCED, WALLS>(state, lam_in, lam_out, gray, links, dmask, g, k, x, y, z, G, dtau);
     // work-group sums of G and d tau through LDS in a fixed order: 224 lanes add 8 lane values
     // each, then one lane per quantity adds those 32 sums
     __shared__ double part[kGradPartials][256];
@@ -1050,6 +1193,17 @@ template <typename F> hipError_t by_storage(int storage, F &&f)
     }
 }
 
+// Whether grids of a lattice and storage can have compact rows (compact_rows).
+template <int LAT, typename S> constexpr bool has_rows() { return LAT != kD2Q9 && sizeof(S) >= 4; }
+
+// f with std::true_type for a grid of compact rows.
+template <int LAT, typename S, typename F> hipError_t by_rows(const Grid &g, F &&f)
+{
+    if constexpr (has_rows<LAT, S>())
+        if (g.nrec) return f(std::true_type{});
+    return f(std::false_type{});
+}
+
 dim3 cell_grid(const Grid &g, int bx, int by)
 {
     return dim3((uint32_t)((g.nx + bx - 1) / bx), (uint32_t)((g.ny + by - 1) / by), (uint32_t)g.nz);
@@ -1074,6 +1228,13 @@ dim3 row_grid(const Grid &g)
 
 hipError_t launch_links(int lattice, const Grid &g, const uint8_t *mask, uint32_t *links, hipStream_t stream)
 {
+    if (g.nrec) {
+        const RowIndex ix = row_index(g, links);
+        hipLaunchKernelGGL(k_row_index, dim3(((uint32_t)g.ny * (uint32_t)g.nz + 3u) / 4u), dim3(256), 0, stream, mask,
+                           const_cast<RowRec *>(ix.rec), const_cast<uint32_t *>(ix.count),
+                           const_cast<uint16_t *>(ix.code), g);
+        return hipGetLastError();
+    }
     return by_lattice(lattice, [&](auto lat) {
         constexpr int LAT = decltype(lat)::value;
         const dim3 grid = row_grid(g), block = row_block(g);
@@ -1090,11 +1251,14 @@ hipError_t launch_init(int lattice, int storage, int order, const Grid &g, const
             using S = decltype(sv);
             constexpr int LAT = decltype(lat)::value;
             const dim3 grid = row_grid(g), block = row_block(g);
-            if (order == 2)
-                hipLaunchKernelGGL((k_init<LAT, S, 2>), grid, block, 0, stream, rho, s, links, (S *)dst, g, k);
-            else
-                hipLaunchKernelGGL((k_init<LAT, S, 3>), grid, block, 0, stream, rho, s, links, (S *)dst, g, k);
-            return hipGetLastError();
+            return by_rows<LAT, S>(g, [&](auto rows) {
+                constexpr bool ROWS = decltype(rows)::value;
+                if (order == 2)
+                    hipLaunchKernelGGL((k_init<LAT, S, 2, ROWS>), grid, block, 0, stream, rho, s, links, (S *)dst, g, k);
+                else
+                    hipLaunchKernelGGL((k_init<LAT, S, 3, ROWS>), grid, block, 0, stream, rho, s, links, (S *)dst, g, k);
+                return hipGetLastError();
+            });
         });
     });
 }
@@ -1129,6 +1293,7 @@ struct StepShape {
     int pull;
     bool cached;
     uint32_t group;
+    uint32_t rows;  // kPullCompact: rows of a work-group
 };
 
 // The rule behind it. All pulls compute the same state bit for bit. Us per step, D3Q19 unless
@@ -1154,6 +1319,12 @@ struct StepShape {
 //    porous medium FP16 2,778 -> 2,647, FP32 4,854 -> 4,812). 16-bit periodic and gray steps take 4
 //    tiles (FP16 320 x 200 x 100 88.8 -> 79.2, 512 x 128 x 128 108.6 -> 104.4), FP32 and FP64 the plain
 //    order (512 x 128 x 128 FP32 204.4 against 206.5; 512^3 3,377 against 3,484 with 2).
+//  * Compact rows: a wave for each 64 cells of a row, in work-groups of one wave: waves past the row's
+//    fluid cells end at once, and in larger work-groups the others wait for room together (ellipsoids
+//    that leave 60% fluid, D3Q27 FP32 256^3: 64 x 1 440, 64 x 2 454, 128 x 1 467, 256 x 1 475, 64 x 4
+//    488). Up to 2 GB of populations two rows, for grids with few solid cells (D3Q19 FP32 128^3 between
+//    two plates 64 x 1 54.9, 64 x 2 52.6; 512 x 128 x 128 207.9 and 201.3; the ellipsoids 48.9 and 51.5,
+//    161.6 and 164.1; D3Q27 256^3 between plates 590 and 601).
 // A launch that the caller has shaped (lbm_set_launch) keeps its boxes and non-temporal stores.
 StepShape step_shape(int mode, int lat, size_t bytes, const Grid &g, int block_x, int flags)
 {
@@ -1164,11 +1335,12 @@ StepShape step_shape(int mode, int lat, size_t bytes, const Grid &g, int block_x
     const bool near = both >= 80e6 && both <= 400e6;
     if (!shaped && g.nx % 64 != 0) {
         const bool whole_lines = g.nx * bytes % 128 == 0;
-        return StepShape{kPullFlat, !whole_lines || both <= 400e6, 16u};
+        return StepShape{kPullFlat, !whole_lines || both <= 400e6, 16u, 1u};
     }
     if (mode != kLinks && !(flags & kLaunchShiftedPull) && g.nx % 64 == 0 && block_x == g.nx)
-        return StepShape{kPullRows, !shaped && near, 1u};
-    return StepShape{kPullShifted, false, group};
+        return StepShape{kPullRows, !shaped && near, 1u, 1u};
+    if (mode == kLinks && g.nrec) return StepShape{kPullCompact, false, group, both <= 2e9 ? 2u : 1u};
+    return StepShape{kPullShifted, false, group, 1u};
 }
 
 hipError_t launch_step(int lattice, int storage, int order, const Grid &g, const StepConsts<double> &k64,
@@ -1185,10 +1357,11 @@ hipError_t launch_step(int lattice, int storage, int order, const Grid &g, const
             const int mode = (flags & kLaunchStreamOnly) ? kStream
                              : gray ? kGray : ((links != nullptr || kc->forced) ? kLinks : kPlain);
             const StepShape sh = step_shape(mode, LAT, sizeof(S), g, block_x, flags);
-            const dim3 block = sh.pull == kPullFlat ? dim3(256) : dim3(block_x, block_y);
+            const bool shaped = !(flags & kLaunchDefault);
+            const dim3 block = sh.pull == kPullFlat ? dim3(256) : (sh.pull == kPullCompact && !shaped ? dim3(64, sh.rows) : dim3(block_x, block_y));
             const dim3 g3 = sh.pull == kPullFlat
                                 ? dim3(((uint32_t)g.nx * (uint32_t)g.ny + 255u) / 256u, 1u, (uint32_t)g.nz)
-                                : cell_grid(g, block_x, block_y);
+                                : cell_grid(g, (int)block.x, (int)block.y);
             TileMap m;
             m.tiles_x = g3.x;
             m.tiles_y = g3.y;
@@ -1215,8 +1388,15 @@ hipError_t launch_step(int lattice, int storage, int order, const Grid &g, const
                 break;                                                                                           \
             }                                                                                                    \
         }                                                                                                        \
+        if constexpr (M == kLinks && has_rows<LAT, S>()) {                                                       \
+            if (sh.pull == kPullCompact) {                                                                       \
+                if (wide) LBM_LAUNCH(O, M, kPullCompactWide, 2); else LBM_LAUNCH(O, M, kPullCompact, 2);         \
+                break;                                                                                           \
+            }                                                                                                    \
+        }                                                                                                        \
         LBM_LAUNCH(O, M, kPullShifted, 2);                                                                       \
     } while (0)
+            const bool wide = (uint64_t)g.zs * (uint32_t)g.nz * sizeof(S) >> 32 != 0;
             if (mode == kStream) {
                 LBM_STEP(3, kStream);
             } else if (order == 2) {
@@ -1264,9 +1444,11 @@ hipError_t launch_moments(int lattice, int storage, const Grid &g, const StepCon
             constexpr int LAT = decltype(lat)::value;
             const dim3 tiles = row_grid(g), block = row_block(g);
             const uint32_t groups = moments_groups(g);
-            hipLaunchKernelGGL((k_moments<LAT, S>), dim3(groups), block, 0, stream, (const S *)src, links, rho, s,
-                               partials, g, k, tiles.x, tiles.y);
-            hipError_t e = hipGetLastError();
+            const hipError_t e = by_rows<LAT, S>(g, [&](auto rows) {
+                hipLaunchKernelGGL((k_moments<LAT, S, decltype(rows)::value>), dim3(groups), block, 0, stream,
+                                   (const S *)src, links, rho, s, partials, g, k, tiles.x, tiles.y);
+                return hipGetLastError();
+            });
             if (e != hipSuccess) return e;
             hipLaunchKernelGGL(k_reduce_partials, dim3(1), dim3(kRedThreads), 0, stream, partials, groups, totals);
             return hipGetLastError();
@@ -1282,13 +1464,16 @@ hipError_t launch_permute(int lattice, int storage, int mode, const Grid &g, con
             using S = decltype(sv);
             constexpr int LAT = decltype(lat)::value;
             const dim3 grid = row_grid(g), block = row_block(g);
-            if (mode == 0)
-                hipLaunchKernelGGL((k_permute<LAT, S, 0>), grid, block, 0, stream, src, dst, links, g, k);
-            else if (mode == 1)
-                hipLaunchKernelGGL((k_permute<LAT, S, 1>), grid, block, 0, stream, src, dst, links, g, k);
-            else
-                hipLaunchKernelGGL((k_permute<LAT, S, 2>), grid, block, 0, stream, src, dst, links, g, k);
-            return hipGetLastError();
+            return by_rows<LAT, S>(g, [&](auto rows) {
+                constexpr bool ROWS = decltype(rows)::value;
+                if (mode == 0)
+                    hipLaunchKernelGGL((k_permute<LAT, S, 0, ROWS>), grid, block, 0, stream, src, dst, links, g, k);
+                else if (mode == 1)
+                    hipLaunchKernelGGL((k_permute<LAT, S, 1, ROWS>), grid, block, 0, stream, src, dst, links, g, k);
+                else
+                    hipLaunchKernelGGL((k_permute<LAT, S, 2, ROWS>), grid, block, 0, stream, src, dst, links, g, k);
+                return hipGetLastError();
+            });
         });
     });
 }
@@ -1305,9 +1490,11 @@ hipError_t launch_seed(int lattice, int storage, const Grid &g, const StepConsts
             const StepConsts<C> *kc;
             if constexpr (sizeof(C) == 8) kc = &k64; else kc = &k32;
             const dim3 tiles = row_grid(g), block = row_block(g);
-            hipLaunchKernelGGL((k_seed<LAT, S>), dim3(moments_groups(g)), block, 0, stream, (const S *)src, (C *)lam,
-                               jpart, g, *kc, kind, plane, links, tiles.x, tiles.y);
-            return hipGetLastError();
+            return by_rows<LAT, S>(g, [&](auto rows) {
+                hipLaunchKernelGGL((k_seed<LAT, S, decltype(rows)::value>), dim3(moments_groups(g)), block, 0, stream,
+                                   (const S *)src, (C *)lam, jpart, g, *kc, kind, plane, links, tiles.x, tiles.y);
+                return hipGetLastError();
+            });
         });
     });
 }
@@ -1330,7 +1517,13 @@ hipError_t launch_adjoint(int lattice, int storage, int order, const Grid &g, co
                        (C *)lam_out, gray, links, dmask, gpart, g, *kc, tiles_x)
 #define LBM_ADJ_L(O, F)                                                                                          \
     do {                                                                                                         \
-        if (links) LBM_ADJ(O, F, true); else LBM_ADJ(O, F, false);                                               \
+        if constexpr (has_rows<LAT, S>()) {                                                                      \
+            if (g.nrec) {                                                                                        \
+                LBM_ADJ(O, F, kCompactRows);                                                                     \
+                break;                                                                                           \
+            }                                                                                                    \
+        }                                                                                                        \
+        if (links) LBM_ADJ(O, F, kLinkWords); else LBM_ADJ(O, F, kNoWalls);                                      \
     } while (0)
             if (order == 2) {
                 if (kc->forced) LBM_ADJ_L(2, true); else LBM_ADJ_L(2, false);
