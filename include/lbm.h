@@ -147,8 +147,9 @@ int64_t lbm_pop_bytes(const lbm_params *p);
  * (32 KiB for FP64), at least 1. For tests and tools; -1 if p is invalid. */
 int64_t lbm_rows_per_block(const lbm_params *p);
 
-/* Bytes of device scratch lbm_init needs (reduction partials, plus 4 bytes per cell of link
- * words or gray fractions when LBM_FLAG_MASK or LBM_FLAG_GRAY is set). -1 if p is invalid. */
+/* Bytes of device scratch lbm_init needs (reduction partials, plus 4 bytes per cell for what the
+ * solid mask becomes or for gray fractions when LBM_FLAG_MASK or LBM_FLAG_GRAY is set). -1 if p is
+ * invalid. */
 int64_t lbm_scratch_bytes(const lbm_params *p);
 
 /* Create a context and write the initial state f_i(0, x) = f^eq_i(rho0(x), s0(x)).
@@ -165,9 +166,10 @@ int64_t lbm_scratch_bytes(const lbm_params *p);
 int lbm_init(lbm_ctx **out, const lbm_params *p, void *pop_a, void *pop_b, void *scratch, const double *rho0,
              const double *s0, const void *mask, void *stream);
 
-/* Advance by nsteps >= 0 steps of eq:LBE_BGK: one fused kernel per step that gathers the
- * streamed populations, forms rho and s, builds f^eq_i and relaxes with 1/tau.
- * Asynchronous. */
+/* Advance by nsteps >= 0 steps of eq:LBE_BGK: fused kernels that gather the streamed populations,
+ * form rho and s, build f^eq_i and relax with 1/tau. A launch makes one step, or, where that is
+ * faster and bitwise the same, two steps (periodic three-dimensional grids in FP32 and FP64) or
+ * several (D2Q9). Asynchronous. */
 int lbm_step(lbm_ctx *ctx, int64_t nsteps);
 
 /* Moments of the current state (eq:a0discrete_f, eq:a1discrete_f).
@@ -211,7 +213,8 @@ int64_t lbm_time(const lbm_ctx *ctx);
 /* Step-kernel launch options: work-group shape block_x * block_y cells (block_x a multiple of
  * 64, block_x * block_y <= 256) and flags. The default spans whole x rows up to 256 cells
  * (block_y = 256 / block_x rows); longer rows take the width of 256, 128 or 64 cells that pads
- * the row least, the widest on a tie. */
+ * the row least, the widest on a tie; rows that are no multiple of 64 cells take 256 consecutive
+ * cells of a z-plane. A launch set here makes one step each. */
 #define LBM_LAUNCH_XCD_SLABS 1    /* hand each of the 8 XCDs one contiguous slab of tiles */
 #define LBM_LAUNCH_SHIFTED_PULL 2 /* pull every population with its own shifted load. By default, when
                                      nx is a multiple of 64 and block_x == nx (work-groups of whole
@@ -275,8 +278,9 @@ int lbm_grad(lbm_ctx *ctx, const lbm_grad_spec *spec, void *workspace, double *o
 int lbm_objective(lbm_ctx *ctx, int32_t objective, int64_t outlet_plane, double *value);
 
 /* Measurement aid: nsteps passes of free streaming (every population moved along its velocity,
- * no collision) with exactly the step kernel's loads and stores, work-group shape and launch.
- * Its time is the data-movement floor of the step. It changes the state (lbm_time does not
+ * no collision) with exactly the one-step kernel's loads and stores, work-group shape and launch.
+ * Its time is the data-movement floor of a step by itself (lbm_step goes below it where a launch
+ * makes two steps). It changes the state (lbm_time does not
  * advance); periodic grids only (LBM_ERR_UNSUPPORTED with a mask or gray field). */
 int lbm_stream_floor(lbm_ctx *ctx, int64_t nsteps);
 

@@ -348,9 +348,9 @@ template <typename C> StepConsts<C> consts_for(const lbm_params &p, const Prepar
 //  * FP64, any size: D3Q19 128^3 102.5 -> 78.0 and 108.0 -> 105.9, 256 x 128 x 128 201 -> 140 and 213.6 ->
 //    209.4, D3Q27 64^3 22.5 -> 20.2 and 23.2 -> 22.9, 128 x 8 x 8 6.5 -> 6.3 and 6.3 -> 6.1. Random
 //    single cells gain nothing until they are many (D3Q19 128^3 with 5% solid 110.8 -> 113.3).
-//  * FP32 from 64 MB on and rows of 128 cells: D3Q27 256^3 588 -> 440 and 588 -> 590, 512^3 4,807 -> 3,401,
-//    D3Q19 128^3 54 -> 51 and 53.9 -> 52.6, 512 x 128 x 128 210 -> 162 and 211 -> 203, 128 x 64 x 64 16.9 ->
-//    16.6; a row index, read before anything else can start, costs more on smaller grids: 128 x 32 x 32
+//  * FP32 from 64 MB on and rows of 128 cells: D3Q27 256^3 588 -> 441 and 588 -> 592, 512^3 4,807 -> 3,347,
+//    128^3 76 -> 64.6 and 75.7 -> 78.6, D3Q19 128^3 53.9 -> 45.7 and 53.9 -> 54.8, 512 x 128 x 128 210 -> 155
+//    and 211 -> 212, 128 x 64 x 64 16.9 -> 15.4; a row index, read before anything else can start, costs more on smaller grids: 128 x 32 x 32
 //    5.5 -> 6.4, 64^3 10.0 -> 10.4 and 8.8 -> 10.2.
 //  * Never for 16-bit storage, where the lookups cost as much as the solid cells' bytes: D3Q27 FP16 256^3
 //    319 -> 304 and 324 -> 329, but 384 -> 471 with 10% random single cells.

@@ -95,12 +95,12 @@ struct lbm_ctx {
     void *pop[2];
     int cur;                 // index of the buffer that holds the current state
     double *partials;        // reduction partials, then the totals (in the caller's scratch)
-    uint32_t *links;         // null without a solid mask
+    uint32_t *links;         // link words or row index (grid.nrec); null without a solid mask
     float *gray;             // null without a gray field
     hipStream_t stream;
     int64_t t;
-    int block_x, block_y;
-    int launch_flags;
+    int block_x, block_y;    // of a launch of one step
+    int launch_flags;        // kLaunchDefault until lbm_set_launch
     lbm::SweepPlan sweep;    // how steps are taken two at a time (tx = 0: they are not)
     lbm::TilePlan tile;      // how several steps of a D2Q9 grid go into one launch (shape -1: none do)
 };

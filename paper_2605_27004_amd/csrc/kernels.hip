@@ -7,7 +7,8 @@
 // canonical pre-collision state is the gather f_i(k, x) = sigma_i + state_i(x - c_i)
 // (periodic wrap). One step is therefore a single pass over HBM: gather q values along
 // -c_i (pull streaming), form rho and s, build the equilibrium, relax, and store q values
-// at the cell itself into the other buffer (eq:LBE_BGK). The initial state is written to
+// at the cell itself into the other buffer (eq:LBE_BGK). (sweep.hip and tile.hip make two and more
+// steps in a pass, with the same arithmetic per cell.) The initial state is written to
 // the same gather positions, and every read-out applies the same gather, so no
 // separate streaming pass exists anywhere.
 //
@@ -20,8 +21,8 @@
 // deviations, rho = rho0 + sum_i g_i and rho s = sum_i g_i c_i (sum_i sigma_i c_i = 0), which
 // keeps FP32 mass conservation at round-off of the deviations rather than of f.
 //
-// The path is bound by HBM bandwidth (2 q sizeof(S) bytes per cell update), so there is no
-// MFMA: each lane owns one cell and loads are coalesced along x. Where a wave lies inside one
+// The path is bound by HBM bandwidth (2 q sizeof(S) bytes per cell update) and holds no contraction, so
+// there is no MFMA: each lane owns one cell and loads are coalesced along x. Where a wave lies inside one
 // grid row, x-shifted pulls load the lane's own x and shift one lane with DPP, exchanging the
 // wave-edge values through LDS (pull_aligned); otherwise the periodic wrap is a per-lane offset
 // select.
@@ -1276,9 +1277,12 @@ hipError_t launch_init(int lattice, int storage, int order, const Grid &g, const
 // The FP32 links step (80 VGPRs, 6 resident) at 4 per CU: 4,962 -> 4,851 us on the 512^3
 // porous medium (3: 4,890, 5: 4,882), where the extra work-groups re-fetched lines. Rows longer
 // than a work-group (shifted pulls), FP32 at 4 per CU: 512^3 3,388 -> 3,339 us, 384^3 unchanged.
-template <int LAT, typename S, int M> unsigned step_lds(unsigned threads)
+// Compact rows take no cap: their loads wait for two lookups first, which more waves hide (D3Q19 FP32
+// 128^3 ellipsoids 53.2 -> 45.8 us, 512 x 128 x 128 166 -> 153, D3Q27 512^3 3,390 -> 3,347).
+template <int LAT, typename S, int M, int P> unsigned step_lds(unsigned threads)
 {
     constexpr bool f32 = std::is_same<S, float>::value, f64 = std::is_same<S, double>::value;
+    if (P == kPullCompact || P == kPullCompactWide) return 0u;
     if (M == kLinks) {  // 4 work-groups of 256 lanes, the same lanes in smaller work-groups
         const unsigned n = 4u * 256u / threads, most = 32u / ((threads + 63u) / 64u);
         return f32 && n < most ? cap_lds(n) : 0u;
@@ -1321,10 +1325,10 @@ struct StepShape {
 //    order (512 x 128 x 128 FP32 204.4 against 206.5; 512^3 3,377 against 3,484 with 2).
 //  * Compact rows: a wave for each 64 cells of a row, in work-groups of one wave: waves past the row's
 //    fluid cells end at once, and in larger work-groups the others wait for room together (ellipsoids
-//    that leave 60% fluid, D3Q27 FP32 256^3: 64 x 1 440, 64 x 2 454, 128 x 1 467, 256 x 1 475, 64 x 4
-//    488). Up to 2 GB of populations two rows, for grids with few solid cells (D3Q19 FP32 128^3 between
-//    two plates 64 x 1 54.9, 64 x 2 52.6; 512 x 128 x 128 207.9 and 201.3; the ellipsoids 48.9 and 51.5,
-//    161.6 and 164.1; D3Q27 256^3 between plates 590 and 601).
+//    that leave 60% fluid, D3Q27 FP32 256^3: 64 x 1 441, 64 x 2 444, 64 x 4 452; FP64 128^3 78.7, 81.3,
+//    84.5). Up to 2 GB of populations two rows, for grids with few solid cells (D3Q19 FP32 128^3 between
+//    two plates 64 x 1 56.6, 64 x 2 54.1; the ellipsoids 45.3 and 45.7; D3Q27 256^3 between plates 592
+//    and 605).
 // A launch that the caller has shaped (lbm_set_launch) keeps its boxes and non-temporal stores.
 StepShape step_shape(int mode, int lat, size_t bytes, const Grid &g, int block_x, int flags)
 {
@@ -1374,7 +1378,7 @@ hipError_t launch_step(int lattice, int storage, int order, const Grid &g, const
             const S *in = (const S *)src;
             S *out = (S *)dst;
 #define LBM_LAUNCH(O, M, P, A)                                                                                     \
-    hipLaunchKernelGGL((k_step<LAT, S, O, M, P, A>), grid, block, (step_lds<LAT, S, M>(threads)), stream, in, out, g, \
+    hipLaunchKernelGGL((k_step<LAT, S, O, M, P, A>), grid, block, (step_lds<LAT, S, M, P>(threads)), stream, in, out, g, \
                        *kc, m, links, gray)
 #define LBM_STEP(O, M)                                                                                           \
     do {                                                                                                         \
