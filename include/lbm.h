@@ -342,7 +342,8 @@ int lbm_batch_init(lbm_batch **out, const lbm_batch_params *p, void *pop_a, void
 
 /* How the steps are run. Results never depend on it (bitwise). */
 #define LBM_BATCH_STEPWISE 0   /* one launch per step, one work-group per 256-cell tile (with
-                                  xcd_group 0, one launch per two steps where that is faster)  */
+                                  xcd_group 0, one launch per two steps, or per several for
+                                  D2Q9, where that is faster)                                  */
 #define LBM_BATCH_PERSISTENT 1 /* one cooperative launch for all steps of an lbm_batch_step  */
 typedef struct lbm_batch_schedule {
     int32_t mode;        /* LBM_BATCH_STEPWISE or LBM_BATCH_PERSISTENT                        */

@@ -172,6 +172,7 @@ struct lbm_batch {
     lbm_batch_schedule sched;
     uint32_t nlaunch;        // tiles in the launch order
     uint32_t nsweep;         // records of the two-step launch in dlaunch's place (0: single steps only)
+    BatchTilePlan tile;      // steps = 0, or the records are for launches of several steps
     uint32_t nwg;            // persistent work-groups
     uint32_t max_chunks;     // largest items-per-domain count of the persistent lists
     // host copies of the schedule (kept alive across the uploads)
@@ -290,6 +291,58 @@ std::vector<BatchSweepRec> plan_sweeps(const Plan &pl, int cu_count)
         best.clear();
         for (const auto &j : jobs) best.push_back(j.second);
     }
+    return best;
+}
+
+// The records of the launch of several two-dimensional steps for a plan, empty where a domain's rows
+// do not fit.
+std::vector<BatchSweepRec> tile_records(const Plan &pl, const BatchTilePlan &p)
+{
+    std::vector<BatchSweepRec> out;
+    for (size_t i = 0; i < pl.dom.size(); ++i) {
+        const Grid &g = pl.dom[i].g;
+        if ((int64_t)g.nx * g.ny <= p.lanes) {
+            out.push_back(BatchSweepRec{(uint32_t)i, 0, g.ny, 0, 1, 0u});
+            continue;
+        }
+        const int fit = p.lanes / g.nx - 2 * (p.steps - 1);
+        if (fit < 1) return {};
+        const int tiles = (g.ny + fit - 1) / fit, rows = (g.ny + tiles - 1) / tiles;
+        for (int y0 = 0; y0 < g.ny; y0 += rows) out.push_back(BatchSweepRec{(uint32_t)i, y0, rows, 0, 1, 0u});
+    }
+    return out;
+}
+
+// Steps per launch and lanes for a batch of planes: the least time by a model of what was measured. A
+// step of a work-group by itself takes 0.70 us with 512 lanes and 0.93 with 1,024; a compute unit makes
+// one step of 1,024 lanes per 1.0 us (FP64 1.5), and 0.3 of a turn is lost at the end; a launch adds 2.2 us
+// and 0.4 of its bytes' time. Single steps take 2.6 us and the bytes at 6.1 TB/s, or at 7.5 where the
+// arrays stay in the Infinity Cache. Us per step, single -> these (FP32, FP64; planes of lo to hi cells a
+// side): 8 of 16 to 64 2.9 -> 1.4, 3.1 -> 1.5; 128 of 10 to 40 3.4 -> 1.6, 4.0 -> 1.7; 128 of 16 to 64 4.4 ->
+// 2.9, 6.5 -> 3.9; 512 of 16 to 64 12.1 -> 6.6, 22.8 -> 9.9; 400 of 90 to 130 59 -> 43, 116 -> 73.
+BatchTilePlan plan_tiles(const Plan &pl, int cu_count, std::vector<BatchSweepRec> &recs)
+{
+    recs.clear();
+    BatchTilePlan best{0, 0};
+    if (pl.lattice != LBM_D2Q9 || (pl.storage != LBM_F32 && pl.storage != LBM_F64)) return best;
+    double cells = 0.0;
+    for (const BatchDomain &d : pl.dom) cells += d.cells;
+    const double per_us = 6.1e6 / (pl.q * pl.bytes);  // cells read or written per us
+    const bool cached = 2.0 * cells * pl.q * pl.bytes <= 300e6;
+    double best_us = 2.6 + 2.0 * cells / per_us * (cached ? 6.1 / 7.5 : 1.0);
+    for (int lanes : {512, 1024})
+        for (int steps : {2, 3, 4, 5, 6, 8, 12, 16}) {
+            const BatchTilePlan p{steps, lanes};
+            std::vector<BatchSweepRec> r = tile_records(pl, p);
+            if (r.empty() || r.size() > 2 * pl.tiles.size()) continue;
+            const double turns = (double)r.size() * lanes / 1024.0 / cu_count;
+            const double step = std::max(lanes == 512 ? 0.70 : 0.93, (turns + 0.3) * (pl.bytes == 8 ? 1.5 : 1.0));
+            const double us = (2.2 + steps * step + 0.4 * ((double)r.size() * lanes + cells) / per_us) / steps;
+            if (us >= best_us) continue;
+            best_us = us;
+            best = p;
+            recs = std::move(r);
+        }
     return best;
 }
 
@@ -417,7 +470,9 @@ int apply_schedule(lbm_batch *b, const lbm_batch_schedule &s)
     if (s.mode == LBM_BATCH_STEPWISE) {
         build_launch_order(b, s.xcd_group != 0);
         b->sweep.clear();
-        if (!s.xcd_group) b->sweep = plan_sweeps(b->pl, b->cu_count);
+        b->tile = BatchTilePlan{0, 0};
+        if (!s.xcd_group) b->tile = plan_tiles(b->pl, b->cu_count, b->sweep);
+        if (!s.xcd_group && !b->tile.steps) b->sweep = plan_sweeps(b->pl, b->cu_count);
         b->nsweep = (uint32_t)b->sweep.size();
         // the records take the place of the launch order, which is then the natural one (dtiles)
         const int rc = b->nsweep
@@ -450,16 +505,19 @@ int run_steps(lbm_batch *b, int64_t nsteps)
     const Plan &pl = b->pl;
     if (b->sched.mode == LBM_BATCH_STEPWISE) {
         for (int64_t left = nsteps; left > 0;) {
-            const bool two = b->nsweep && left >= 2;
+            const bool two = b->nsweep && !b->tile.steps && left >= 2;
+            const int many = b->tile.steps ? (int)std::min<int64_t>(left, b->tile.steps) : 0;
             const hipError_t e =
-                two ? launch_batch_sweep(pl.lattice, pl.storage, pl.order, b->nsweep, (const BatchSweepRec *)b->dlaunch,
+                many ? launch_batch_tile(pl.storage, pl.order, b->nsweep, (const BatchSweepRec *)b->dlaunch, b->ddom, b->dk64,
+                                         b->dk32, b->pop[b->cur], b->pop[1 - b->cur], many, b->tile, b->stream)
+                : two ? launch_batch_sweep(pl.lattice, pl.storage, pl.order, b->nsweep, (const BatchSweepRec *)b->dlaunch,
                                          b->ddom, b->dk64, b->dk32, b->pop[b->cur], b->pop[1 - b->cur], b->stream)
                     : launch_batch_step(pl.lattice, pl.storage, pl.order, b->nlaunch, b->nsweep ? b->dtiles : b->dlaunch,
                                         b->ddom, b->dk64, b->dk32, b->pop[b->cur], b->pop[1 - b->cur],
                                         2 * pl.pop_elems * pl.bytes <= 300000000, b->stream);
             if (e != hipSuccess) return fail_hip(e, "batch step launch");
             b->cur = 1 - b->cur;
-            left -= two ? 2 : 1;
+            left -= many ? many : (two ? 2 : 1);
         }
         return LBM_OK;
     }

@@ -75,6 +75,17 @@ hipError_t launch_batch_sweep(int lattice, int storage, int order, uint32_t nrec
                               const BatchDomain *doms, const StepConsts<double> *k64, const StepConsts<float> *k32,
                               const void *src, void *dst, hipStream_t stream);
 
+// Several steps of every two-dimensional domain in one launch (batch_tile.hip): at most `steps` of
+// them by work-groups of `lanes` lanes. The records' rows are y0 .. y0 + rows - 1, all of them or with a rim
+// of steps - 1 more on both sides (nx times all of these <= lanes).
+struct BatchTilePlan {
+    int steps;  // 0: single steps
+    int lanes;  // 512 or 1024
+};
+hipError_t launch_batch_tile(int storage, int order, uint32_t nrecs, const BatchSweepRec *recs, const BatchDomain *doms,
+                             const StepConsts<double> *k64, const StepConsts<float> *k32, const void *src, void *dst,
+                             int steps, const BatchTilePlan &p, hipStream_t stream);
+
 struct PersistArgs {
     void *pop0, *pop1;
     uint32_t parity;          // step t reads pop[(parity + t) & 1] and writes the other
