@@ -246,11 +246,13 @@ void build_launch_order(lbm_batch *b, bool xcd)
 
 // The two-step launch's records, largest first (work-groups start in this order, so the last to
 // run are the shortest); none where two single steps are the faster way or a domain's rows are too
-// long. A record takes (planes + 2) x (waves of its rows) x row_us; the z-planes of a domain are cut into
-// runs of at most `len` planes, the len of least time over the compute units. Against that stands
-// the single step: 2 us a launch and the bytes at 6.1 TB/s. So many small domains sweep and a few do
-// not (us per step, single against sweep, D3Q19 FP32: 128 domains of 16 to 64 cells a side 210 / 173, 64
-// of 10 to 40 29.6 / 29.1, 22 of 15 to 46 21.3 / 22.0).
+// long. A record takes (planes + 2) x (0.72 waves of its rows + 0.325 waves of a full tile) x row_us: a
+// small cross-section has a compute unit to itself all the same, and its planes' latency. The
+// z-planes of a domain are cut into runs of at most `len` planes, the len of least time over the
+// compute units. Against that stands the single step: 2 us a launch and the bytes at 6.1 TB/s. So
+// large domains sweep, and small ones in FP64 (us per step, single against sweep: D3Q19 FP32 100 domains
+// of 16 to 64 cells a side 155 / 135, 50 of 20 to 60 74.9 / 74.2, 128 of 10 to 40 56.5 / 63.4, FP64 116 / 96.5;
+// D3Q27 FP32 100 of 16 to 64 222 / 201, 119 of 12 to 42 89.1 / 89.6, 128 of 10 to 40 81.5 / 84.1, FP64 165 / 155).
 std::vector<BatchSweepRec> plan_sweeps(const Plan &pl, int cu_count)
 {
     std::vector<BatchSweepRec> best;
@@ -262,7 +264,8 @@ std::vector<BatchSweepRec> plan_sweeps(const Plan &pl, int cu_count)
         bytes += 2.0 * pl.q * pl.bytes * d.cells;
     }
     const double row_us = 0.42 * (pl.q / 19.0) * (pl.bytes == 8 ? 1.72 : 1.0);
-    double best_us = 2.0 * (2.0 + bytes / 6.1e6) / 1.05;
+    const double full = 0.325 * ((cols + 63) / 64);
+    double best_us = 2.0 * (2.0 + bytes / 6.1e6) / 1.03;
     for (int len : {64, 48, 32, 24, 16, 12, 8, 6, 4}) {
         std::vector<std::pair<double, BatchSweepRec>> jobs;
         double total = 0.0, most = 0.0;
@@ -278,7 +281,8 @@ std::vector<BatchSweepRec> plan_sweeps(const Plan &pl, int cu_count)
                     if (y0 >= g.ny) break;
                     const BatchSweepRec r{(uint32_t)i, y0, rows, (int32_t)((int64_t)g.nz * s / segs),
                                           (int32_t)((int64_t)g.nz * (s + 1) / segs), 0u};
-                    const double us = (r.z1 - r.z0 + 2) * (double)((g.nx * (whole ? rows : rows + 2) + 63) / 64) * row_us;
+                    const int waves = (g.nx * (whole ? rows : rows + 2) + 63) / 64;
+                    const double us = (r.z1 - r.z0 + 2) * (0.72 * waves + full) * row_us;
                     total += us;
                     most = std::max(most, us);
                     jobs.emplace_back(us, r);
