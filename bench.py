@@ -2,19 +2,21 @@
 """Benchmark of the fused anisotropic-equilibrium BGK stream-collide step on one MI355X.
 
 Workload: D3Q19 256^3 periodic, FP32 deviations, seeded random SPD tensor (seed 0),
-tau = 0.7, 3-D Taylor-Green initial state u0 = 0.02 -- one "step" is one fused
-stream-and-collide pass over the whole grid. Prints ONE JSON line:
+tau = 0.7, 3-D Taylor-Green initial state u0 = 0.02 -- one "step" is one stream-and-collide update of
+the whole grid; on this grid a launch makes two of them in one pass over HBM. Prints ONE JSON line:
 
   value        whole-job MLUPS (cells * steps / time / 1e6), inputs resident in HBM
-  roofline     the step kernel against the 8 TB/s HBM peak: achieved = algorithmic bytes per
-               launch (2 q sizeof(float) = 152 B per cell) / mean kernel time from HIP events
-               on the launch stream; traffic = HBM bytes per launch from rocprofv3 counters
-               (profiles/), null if the kernel source changed since they were taken; beside
-               it the plain copy kernel's bandwidth and the time of free streaming with the
-               step's own loads and stores (its data-movement floor)
+  roofline     the kernel that makes the steps against the 8 TB/s HBM peak: achieved = the bytes
+               that a launch must move (every population read once and written once: 2 q
+               sizeof(float) = 152 B per cell for its two steps) / mean launch time from HIP
+               events on the launch stream; traffic = HBM bytes per launch from rocprofv3
+               counters (profiles/), null if the kernel source changed since they were taken;
+               beside it the plain copy kernel's bandwidth and the time of one pass of free
+               streaming (the data-movement floor of a single step)
   cpu_baseline the FP64 oracle on the host cores, a bounded sample of the same workload
   variants     FP16 / BF16 shifted-deviation storage and FP64 storage of the same workload:
-               MLUPS, roofline fraction and the per-field error against the FP64 path; the
+               MLUPS, roofline fraction (bytes counted as above: FP64 makes two steps in a
+               pass, the 16-bit storages one) and the per-field error against the FP64 path; the
                FP32 step with the second-order equilibrium (cost of the third-order term)
   adjoint      gradient workload (D2Q9 512^2 and D3Q19 128^3 channels with gray obstacles,
                2000 steps, checkpoints every 100, FP32): time of lbm_grad (forward + reverse
@@ -22,7 +24,7 @@ stream-and-collide pass over the whole grid. Prints ONE JSON line:
   porous       D3Q27 porous medium (ellipsoid mask, porosity 0.6, halfway bounce-back, body
                force 1e-6, tensor cs^2 diag(1.5, 1, 0.5), tau = 0.9), FP64 / FP32 / FP16 / BF16:
                MLUPS, fraction of peak on the useful bytes (fluid cells' populations plus the
-               link words) and each precision's error against the FP64 path after 1000 steps
+               row index or the link words) and each precision's error against the FP64 path after 1000 steps
   batched      512 independent D3Q19 domains (edges 16..64, own tensor and tau each), FP32,
                500 steps: the autotuned schedule's MLUPS and fraction of the 8 TB/s peak, beside
                fixed step-per-launch and persistent schedules
@@ -54,9 +56,15 @@ sys.path.insert(0, ROOT)
 PEAK_GBPS = 8000.0  # MI355X HBM3E
 METRIC = "MLUPS & % of HBM peak, D3Q19 256^3 fp32 vs fp16-shifted; adjoint/fwd ratio"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_step_d3q19_f32_256.txt")
-# the step kernel's source: the kernel file and the per-cell header it instantiates
+# the two-step kernel's source: the kernel file and the headers it instantiates
 KERNEL_SRCS = [os.path.join(ROOT, "paper_2605_27004_amd", "csrc", f)
-               for f in ("kernels.hip", "cell.hpp", "common.hpp", "lattice.hpp")]
+               for f in ("sweep.hip", "sweep.hpp", "cell.hpp", "common.hpp", "lattice.hpp")]
+
+
+def launches(steps, storage):
+    """Passes over HBM that `steps` steps of the periodic D3Q19 grid take: two steps each in FP32 and
+    FP64 (an odd last step has its own), one in 16-bit storage."""
+    return (steps + 1) // 2 if storage in ("f32", "f64") else steps
 
 
 def parse():
@@ -93,7 +101,7 @@ LEGS = {
     "porous-bf16": ("D3Q27 porous medium 512^3, BF16-shifted (links step with body force)", "porous", "bf16"),
     "porous-f64": ("D3Q27 porous medium 512^3, FP64 (links step with body force)", "porous", "f64"),
     "adjoint-d3q19": ("gradient workload D3Q19 128^3, FP32: lbm_grad over --steps steps", "adjoint", "f32"),
-    "batched": ("512 batched D3Q19 domains, FP32, step per launch (domain-major tiles)", "batched", "f32"),
+    "batched": ("512 batched D3Q19 domains, FP32, domain-major tiles (two steps per launch)", "batched", "f32"),
     "batched-xcd": ("512 batched D3Q19 domains, FP32, step per launch (each domain's tiles on one XCD)", "batched",
                     "f32"),
     "batched-persistent": ("512 batched D3Q19 domains, FP32, one cooperative launch (2 work-groups per CU, "
@@ -173,7 +181,7 @@ def kernel_sha():
 
 
 def traffic_per_launch():
-    """HBM bytes per step launch from the committed rocprofv3 counter summary (FETCH_SIZE and
+    """HBM bytes per two-step launch from the committed rocprofv3 counter summary (FETCH_SIZE and
     WRITE_SIZE, scaled by the copy-kernel calibration), or None when the kernel source has
     changed since the counters were taken."""
     try:
@@ -273,7 +281,8 @@ def main():
     else:
         secs, run_secs = timed_steps(sim, args.steps, args.warmup, torch), None
     mlups = cells * args.steps / secs / 1e6
-    kernel_s = secs / args.steps
+    step_s = secs / args.steps
+    kernel_s = secs / launches(args.steps, "f32")
     alg_bytes = 2 * q * 4 * cells
     achieved = alg_bytes / kernel_s / 1e9
     _, _, tot = sim.moments(fields=False)
@@ -297,7 +306,7 @@ def main():
         "n_gpus": 1,
         "steps": args.steps,
         "warmup": args.warmup,
-        "ms_per_step": round(kernel_s * 1e3, 5),
+        "ms_per_step": round(step_s * 1e3, 5),
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
@@ -309,7 +318,7 @@ def main():
                    "parallelism": "single GPU"},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_GBPS, "unit": "GB/s",
                      "frac": round(achieved / PEAK_GBPS, 4), "traffic": traffic_per_launch(),
-                     "algorithmic_bytes_per_launch": alg_bytes, "kernel": "k_step<D3Q19, float, order 3, plain>",
+                     "algorithmic_bytes_per_launch": alg_bytes, "kernel": "k_sweep<D3Q19, float, order 3> (two steps)",
                      "copy_kernel_GBps": round(copy_gbps, 1), "frac_of_copy": round(achieved / copy_gbps, 4),
                      "stream_floor_us": round(floor_s * 1e6, 1), "frac_of_stream_floor": round(floor_s / kernel_s, 4)},
         "mass_total": tot[0],
@@ -317,7 +326,7 @@ def main():
                    "run_ms_per_step": None if run_secs is None else [round(t / args.steps * 1e3, 5) for t in run_secs]},
     }
 
-    progress(f"headline done: {kernel_s * 1e6:.1f} us per step")
+    progress(f"headline done: {step_s * 1e6:.1f} us per step")
     # ---- storage variants: speed and error against the FP64 path at full size ----
     if not args.no_variants:
         def run_fields(storage, steps):
@@ -338,7 +347,7 @@ def main():
             del s_
             torch.cuda.empty_cache()
             v = {"MLUPS": round(cells * n_ / t_ / 1e6, 1),
-                 "frac": round(2 * q * sz * cells / (t_ / n_) / 1e9 / PEAK_GBPS, 4),
+                 "frac": round(2 * q * sz * cells * launches(n_, storage) / t_ / 1e9 / PEAK_GBPS, 4),
                  "us_per_step": round(t_ / n_ * 1e6, 2), "timed_steps": n_, "warmup_steps": w_}
             if storage != "f64":
                 got = run_fields(storage, wl.steps)
@@ -353,7 +362,7 @@ def main():
         t_ = timed_steps(s_, n_, w_, torch)
         del s_
         variants["f32_order2"] = {"MLUPS": round(cells * n_ / t_ / 1e6, 1),
-                                  "frac": round(2 * q * 4 * cells / (t_ / n_) / 1e9 / PEAK_GBPS, 4),
+                                  "frac": round(2 * q * 4 * cells * launches(n_, "f32") / t_ / 1e9 / PEAK_GBPS, 4),
                                   "us_per_step": round(t_ / n_ * 1e6, 2), "timed_steps": n_, "warmup_steps": w_}
         del got, ref
         torch.cuda.empty_cache()
@@ -401,7 +410,9 @@ def main():
             s3 = lbm.Simulation(p3, wl3.rho, wl3.s, mask=mask)
             n3 = 50
             t3 = timed_steps(s3, n3, 10, torch) / n3
-            useful = fluid * 2 * 27 * sz + wl3.cells * 4
+            # FP64 and FP32 read a row index (2 bytes per fluid cell, 8 per 30 cells), the 16-bit
+            # storages a link word per cell
+            useful = fluid * 2 * 27 * sz + (wl3.cells * 4 if sz == 2 else fluid * 2 + wl3.cells * 8 // 30)
             rec = {"MLUPS": round(wl3.cells / t3 / 1e6, 1), "fluid_MLUPS": round(fluid / t3 / 1e6, 1),
                    "frac": round(useful / t3 / 1e9 / PEAK_GBPS, 4), "ms_per_step": round(t3 * 1e3, 4)}
             s3.step(wl3.steps - n3 - 10)
@@ -448,13 +459,16 @@ def main():
             bt.status()
             return e0.elapsed_time(e1) / 1e3
 
-        def figures(sec):
+        def figures(sec, sch):
+            # one launch per step in domain-major order makes two steps of every domain in a pass
+            two = sch["mode"] == "stepwise" and not sch["xcd_group"]
+            passes = launches(wl5.steps, "f32") if two else wl5.steps
             return {"MLUPS": round(wl5.cells * wl5.steps / sec / 1e6, 1),
-                    "frac": round(152.0 * wl5.cells * wl5.steps / sec / 1e9 / PEAK_GBPS, 4),
+                    "frac": round(152.0 * wl5.cells * passes / sec / 1e9 / PEAK_GBPS, 4),
                     "ms_per_step": round(sec / wl5.steps * 1e3, 4)}
 
         res = {"domains": len(wl5.domains), "cells": wl5.cells, "steps": wl5.steps, "storage": "f32",
-               "autotuned": dict(schedule=chosen, trial_ms_per_step=round(tune_ms, 4), **figures(time_batch(wl5.steps)))}
+               "autotuned": dict(schedule=chosen, trial_ms_per_step=round(tune_ms, 4), **figures(time_batch(wl5.steps), chosen))}
         fixed = {"stepwise_xcd": dict(mode="stepwise", xcd_group=1),
                  "persistent_all": dict(mode="persistent", xcd_group=1, wg_per_cu=2, chunk_cells=65536, group_bytes=0),
                  "persistent_groups": dict(mode="persistent", xcd_group=1, wg_per_cu=2, chunk_cells=4096,
@@ -463,7 +477,7 @@ def main():
             if args.batched_stepwise_only and sch["mode"] != "stepwise":
                 continue
             bt.set_schedule(**sch)
-            res[name] = figures(time_batch(wl5.steps))
+            res[name] = figures(time_batch(wl5.steps), sch)
         bt.close()
         del bt
         torch.cuda.empty_cache()

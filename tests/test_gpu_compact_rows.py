@@ -129,10 +129,15 @@ def test_gradient_over_rows_of_fluid_cells(lattice, storage, shape, times, objec
     a cell's share is spread over them)."""
     a, b = _sims(lattice, storage, shape, times, 0.3, 3)
     k = times if objective == "kinetic_energy" else 1
-    ja, ta, ua, _ = a.grad(objective, 12, 4, 5, want_dmask=False)
-    jb, tb, ub, _ = b.grad(objective, 12, 4, 5, want_dmask=False)
+    ja, ta, ua, ma = a.grad(objective, 12, 4, 5)
+    jb, tb, ub, mb = b.grad(objective, 12, 4, 5)
     tol = 1e-9 if storage == "f64" else 2e-5
     ta, tb = np.asarray(ta), np.asarray(tb)
     assert abs(jb - k * ja) <= tol * abs(k * ja)
     assert np.abs(tb - k * ta).max() <= tol * np.abs(k * ta).max()
     assert abs(ub - k * ua) <= tol * abs(k * ua)
+    # a cell's own sensitivity: of the energy the same in every copy, of the flux shared out over them
+    nx, ny, nz = shape
+    ma, mb = ma.reshape(nz, ny, 1, nx), mb.reshape(nz, ny, times, nx)
+    got = mb if k == times else mb.sum(dim=2, keepdim=True)
+    assert (got - ma).abs().max().item() <= tol * ma.abs().max().item()
