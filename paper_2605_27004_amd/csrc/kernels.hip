@@ -567,14 +567,16 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_partials(const double *_
     if (tid < kPartials) totals[tid] = red[tid][0];
 }
 
-// Canonical-order permutations of the state (see the file header and Slot).
-template <int LAT, typename S, int MODE, bool ROWS>
+// Canonical-order permutations of the state (see the file header and Slot). HBM bounds them; with a load,
+// a branch and a store for each direction in turn, the latencies did (NT: non-temporal stores of an
+// export). Us before -> after, bytes at a copy's rate: D3Q27 384^3 FP16 with a mask 2,446 -> 1,149 (920),
+// 256^3 FP32 with a mask 717 -> 562 (545), import 1,111 -> 749; D3Q19 256^3 FP16 350 -> 214 (192).
+template <int LAT, typename S, int MODE, bool ROWS, bool NT>
 __global__ __launch_bounds__(256) void k_permute(const void *__restrict__ in, void *__restrict__ out,
                                                  const uint32_t *__restrict__ links, const Grid g,
                                                  const StepConsts<double> k)
 {
     using L = Lattice<LAT>;
-    constexpr int NP = L::NP;
     const int32_t x = blockIdx.x * blockDim.x + threadIdx.x;
     const int32_t y = blockIdx.y * blockDim.y + threadIdx.y;
     const int32_t z = blockIdx.z;
@@ -582,24 +584,38 @@ __global__ __launch_bounds__(256) void k_permute(const void *__restrict__ in, vo
     const auto c = walled_cell<ROWS>(g, links, x, y, z);
     const uint32_t lk = link_word(c, links);
     const bool solid = lk & 1u;
-    auto move = [&](int i, Slot sl, double sigma) {
-        if constexpr (MODE == 0) {
-            st_at(plane((S *)out, i, g.n), c.own,
-                  solid ? Conv<S>::st(typename Conv<S>::C(0)) : ld_slot((const S *)in, g, sl));
-        } else if constexpr (MODE == 1) {
-            if (!solid) st_slot((S *)out, g, sl, ld_at(plane((const S *)in, i, g.n), c.own));
-        } else {
-            // FP64 output: 8 bytes per cell, so 64-bit indexing (the storage-type planes above
-            // stay below 4 GiB, this one need not)
-            const double v = solid ? 0.0 : (double)Conv<S>::ld(ld_slot((const S *)in, g, sl)) + sigma;
-            ((double *)out)[(size_t)i * g.n + c.own] = v;
-        }
+    // all loads before the first store, and one branch for a solid cell: its values are zero
+    const auto slot = [&](int i) {
+        if (i == 0) return fixed_slot(0, own_ref(c));
+        return i & 1 ? slot_plus<LAT>(c, (i - 1) / 2, lk) : slot_minus<LAT>(c, (i - 1) / 2, lk);
     };
-    move(0, fixed_slot(0, own_ref(c)), k.sigma[0]);
+    S v[L::Q];
+    if constexpr (MODE == 1) {
+        if (solid) return;
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
-        move(2 * p + 1, slot_plus<LAT>(c, p, lk), k.sigma[p + 1]);
-        move(2 * p + 2, slot_minus<LAT>(c, p, lk), k.sigma[p + 1]);
+        for (int i = 0; i < L::Q; ++i) v[i] = ld_at(plane((const S *)in, i, g.n), c.own);
+#pragma unroll
+        for (int i = 0; i < L::Q; ++i) st_slot((S *)out, g, slot(i), v[i]);
+    } else {
+        if (solid) {
+#pragma unroll
+            for (int i = 0; i < L::Q; ++i) v[i] = Conv<S>::st(typename Conv<S>::C(0));
+        } else {
+#pragma unroll
+            for (int i = 0; i < L::Q; ++i) v[i] = ld_slot((const S *)in, g, slot(i));
+        }
+#pragma unroll
+        for (int i = 0; i < L::Q; ++i) {
+            if constexpr (MODE == 0) {
+                if (NT) __builtin_nontemporal_store(v[i], plane((S *)out, i, g.n) + c.own);
+                else st_at(plane((S *)out, i, g.n), c.own, v[i]);
+            } else {
+                // FP64 output: 8 bytes per cell, so 64-bit indexing (the storage-type planes above
+                // stay below 4 GiB, this one need not)
+                const double sigma = solid ? 0.0 : k.sigma[(i + 1) / 2];
+                ((double *)out)[(size_t)i * g.n + c.own] = (double)Conv<S>::ld(v[i]) + sigma;
+            }
+        }
     }
 }
 
@@ -1460,6 +1476,9 @@ hipError_t launch_moments(int lattice, int storage, const Grid &g, const StepCon
     });
 }
 
+// Work-groups of whole rows, or of the widest part that long rows are a multiple of (384^3 FP16: 128 cells
+// 1,149 us, 256 1,434). Exports of rows of whole cache lines go past the caches (D3Q19 FP32 256^3 472 -> 437;
+// D3Q27 FP32 150 x 101 x 75 the other way round, 47 against 64).
 hipError_t launch_permute(int lattice, int storage, int mode, const Grid &g, const StepConsts<double> &k,
                           const uint32_t *links, const void *src, void *dst, hipStream_t stream)
 {
@@ -1467,15 +1486,23 @@ hipError_t launch_permute(int lattice, int storage, int mode, const Grid &g, con
         return by_storage(storage, [&](auto sv) {
             using S = decltype(sv);
             constexpr int LAT = decltype(lat)::value;
-            const dim3 grid = row_grid(g), block = row_block(g);
+            const bool lines = g.nx * (int64_t)sizeof(S) % 128 == 0;
+            dim3 block = row_block(g);
+            if (g.nx > 256 && g.nx % 64 == 0) {
+                const int bx = g.nx % 256 == 0 ? 256 : (g.nx % 128 == 0 ? 128 : 64);
+                block = dim3((uint32_t)bx, (uint32_t)(256 / bx));
+            }
+            const dim3 grid = cell_grid(g, (int)block.x, (int)block.y);
             return by_rows<LAT, S>(g, [&](auto rows) {
                 constexpr bool ROWS = decltype(rows)::value;
-                if (mode == 0)
-                    hipLaunchKernelGGL((k_permute<LAT, S, 0, ROWS>), grid, block, 0, stream, src, dst, links, g, k);
+                if (mode == 0 && lines)
+                    hipLaunchKernelGGL((k_permute<LAT, S, 0, ROWS, true>), grid, block, 0, stream, src, dst, links, g, k);
+                else if (mode == 0)
+                    hipLaunchKernelGGL((k_permute<LAT, S, 0, ROWS, false>), grid, block, 0, stream, src, dst, links, g, k);
                 else if (mode == 1)
-                    hipLaunchKernelGGL((k_permute<LAT, S, 1, ROWS>), grid, block, 0, stream, src, dst, links, g, k);
+                    hipLaunchKernelGGL((k_permute<LAT, S, 1, ROWS, false>), grid, block, 0, stream, src, dst, links, g, k);
                 else
-                    hipLaunchKernelGGL((k_permute<LAT, S, 2, ROWS>), grid, block, 0, stream, src, dst, links, g, k);
+                    hipLaunchKernelGGL((k_permute<LAT, S, 2, ROWS, false>), grid, block, 0, stream, src, dst, links, g, k);
                 return hipGetLastError();
             });
         });
