@@ -1333,6 +1333,9 @@ struct StepShape {
 //    D3Q27 FP32 129 x 100 x 90 67.6 -> 50.8, FP16 45.4 -> 29.4. Runs with non-temporal stores are no
 //    better than boxes there (FP16 129 x 100 x 90 21.9). Rows of whole lines (96 cells in FP32) take
 //    them on large grids all the same, as above.
+//    Gray grids of 12 to 32 MB whose boxes leave few lanes idle keep the boxes: 57 x 47 x 77 FP16 6.62 against
+//    7.05, FP32 9.03 against 9.63 (62 x 80 x 80 10.26 and 10.43; without gray cells 6.48 against 6.26; smaller,
+//    60 x 30 x 30, 4.46 against 3.98; larger, 120 x 60 x 60, 10.76 against 9.89).
 //  * Longer rows of a multiple of 64 cells, and the links step on any multiple: boxes, shifted
 //    loads, non-temporal stores. In the links step the tiles of a row share an XCD: its shifted
 //    and bounce-back pulls read lines that they share, which the L2 then serves once (512^3
@@ -1353,6 +1356,9 @@ StepShape step_shape(int mode, int lat, size_t bytes, const Grid &g, int block_x
     const double q = lat == kD2Q9 ? 9 : (lat == kD3Q19 ? 19 : 27);
     const double both = 2.0 * q * (double)bytes * g.n;
     const bool near = both >= 80e6 && both <= 400e6;
+    const int32_t lanes = (g.nx + 63) / 64 * 64;
+    const bool boxes = mode == kGray && both >= 12e6 && both <= 32e6 && 20ll * g.nx >= 17ll * lanes;
+    if (!shaped && g.nx % 64 != 0 && boxes) return StepShape{kPullShifted, false, 1u, 1u};
     if (!shaped && g.nx % 64 != 0) {
         const bool whole_lines = g.nx * bytes % 128 == 0;
         return StepShape{kPullFlat, !whole_lines || both <= 400e6, 16u, 1u};

@@ -28,6 +28,7 @@ def _need_gpu():
     ("D3Q27", "f64", (50, 21, 14), "gray", 3), ("D3Q19", "f64", (17, 16, 16), "mask", 2),
     ("D3Q19", "f32", (96, 40, 40), "gray", 3), ("D3Q19", "f16", (128, 96, 96), "gray", 3),
     ("D3Q27", "f16", (320, 12, 10), "none", 3), ("D3Q19", "f32", (160, 180, 110), "gray", 3),
+    ("D3Q19", "f32", (57, 47, 40), "gray", 3), ("D3Q19", "f16", (62, 80, 80), "gray", 2),
 ])
 def test_launch_of_runs_is_launch_of_boxes(lattice, storage, shape, walls, order):
     rho, s = W.random_fields(shape, 3, 17)
