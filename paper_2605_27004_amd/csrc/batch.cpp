@@ -832,7 +832,7 @@ int lbm_batch_moments(lbm_batch *b, double *rho, double *s, double *totals)
     if (rc) return rc;
     const Plan &pl = b->pl;
     const size_t bytes = pl.dom.size() * 4 * sizeof(double);
-    HostSlot slot(totals ? bytes : SIZE_MAX);
+    HostSlot slot(totals ? bytes : SIZE_MAX, b->stream);
     hipError_t e = launch_batch_moments(pl.lattice, pl.storage, (uint32_t)pl.tiles.size(), b->dtiles, b->ddom,
                                         b->dk64, b->pop[b->cur], rho, s, (uint64_t)pl.cells, b->dpart,
                                         (uint32_t)pl.dom.size(), slot.p ? slot.p : b->dtot, b->stream);
@@ -840,7 +840,7 @@ int lbm_batch_moments(lbm_batch *b, double *rho, double *s, double *totals)
     if (!totals) return LBM_OK;
     std::vector<double> h(pl.dom.size() * 4);
     if (!slot.p) e = hipMemcpyAsync(h.data(), b->dtot, bytes, hipMemcpyDeviceToHost, b->stream);
-    if (e == hipSuccess) e = slot.wait(b->stream);
+    if (e == hipSuccess) e = slot.wait();
     if (e != hipSuccess) return fail_hip(e, "totals copy");
     if (slot.p) std::memcpy(h.data(), slot.p, bytes);
     for (size_t d = 0; d < pl.dom.size(); ++d) {

@@ -51,7 +51,7 @@ uint32_t g_slots_taken = 0;  // bit i: place i belongs to a call
 
 }  // namespace
 
-HostSlot::HostSlot(size_t bytes) : p(nullptr), at_(-1)
+HostSlot::HostSlot(size_t bytes, hipStream_t stream) : p(nullptr), stream_(stream), at_(-1), waited_(false)
 {
     if (bytes > kSlotBytes) return;
     std::lock_guard<std::mutex> guard(g_slots_lock);
@@ -80,14 +80,18 @@ HostSlot::HostSlot(size_t bytes) : p(nullptr), at_(-1)
 HostSlot::~HostSlot()
 {
     if (at_ < 0) return;
+    if (!waited_ && wait() != hipSuccess) {
+        (void)hipGetLastError();  // the call has reported what failed first
+        return;
+    }
     std::lock_guard<std::mutex> guard(g_slots_lock);
     g_slots_taken &= ~(1u << at_);
 }
 
-hipError_t HostSlot::wait(hipStream_t stream)
+hipError_t HostSlot::wait()
 {
-    const hipError_t e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) at_ = -1;
+    const hipError_t e = hipStreamSynchronize(stream_);
+    waited_ = e == hipSuccess;
     return e;
 }
 
@@ -607,13 +611,13 @@ namespace host {
 int moments_with(lbm_ctx *c, double *rho, double *s, double *totals, double *partials, double *dtot, bool pinned)
 {
     double h[kPartials];
-    HostSlot slot(totals && pinned ? sizeof h : SIZE_MAX);
+    HostSlot slot(totals && pinned ? sizeof h : SIZE_MAX, c->stream);
     hipError_t e = launch_moments(c->p.lattice, c->p.storage, c->grid, c->k64, c->links, c->pop[c->cur], rho, s,
                                   partials, slot.p ? slot.p : dtot, c->stream);
     if (e != hipSuccess) return fail_hip(e, "moments kernel launch");
     if (!totals) return LBM_OK;
     if (slot.p) {
-        e = slot.wait(c->stream);
+        e = slot.wait();
         if (e == hipSuccess) std::memcpy(h, slot.p, sizeof h);
     } else {
         e = hipMemcpyAsync(h, dtot, sizeof h, hipMemcpyDeviceToHost, c->stream);
@@ -769,7 +773,7 @@ int lbm_grad(lbm_ctx *c, const lbm_grad_spec *spec, void *workspace, double *obj
     // seed the reverse sweep with dJ/df at the final state
     void *lam_in = ws + l.lam_a, *lam_out = ws + l.lam_b;
     double h[1 + kGradPartialsHost];
-    HostSlot slot(sizeof h);
+    HostSlot slot(sizeof h, st);
     double *gpart = (double *)(ws + l.gpart), *jpart = (double *)(ws + l.jpart);
     double *sums = slot.p ? slot.p : (double *)(ws + l.sums);
     e = launch_seed(c->p.lattice, c->p.storage, c->grid, c->k64, c->k32, c->pop[c->cur], lam_in, jpart,
@@ -794,7 +798,7 @@ int lbm_grad(lbm_ctx *c, const lbm_grad_spec *spec, void *workspace, double *obj
     }
     e = launch_sum(gpart, na, kGradPartialsHost, sums + 1, st);
     if (e == hipSuccess && !slot.p) e = hipMemcpyAsync(h, sums, sizeof h, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = slot.wait(st);
+    if (e == hipSuccess) e = slot.wait();
     if (e != hipSuccess) return fail_hip(e, "gradient read-back");
     if (slot.p) std::memcpy(h, slot.p, sizeof h);
     *objective = h[0];
@@ -855,13 +859,13 @@ int lbm_objective(lbm_ctx *c, int32_t objective, int64_t outlet_plane, double *v
                     (long long)(c->p.nx - 1));
     // the moments partials hold one double per seed work-group, the totals slot the sum
     double *jpart = c->partials;
-    HostSlot slot(sizeof(double));
+    HostSlot slot(sizeof(double), c->stream);
     double *sum = slot.p ? slot.p : c->partials + kPartials * (size_t)moments_groups(c->grid);
     hipError_t e = launch_seed(c->p.lattice, c->p.storage, c->grid, c->k64, c->k32, c->pop[c->cur], nullptr, jpart,
                                objective, (int)outlet_plane, c->links, c->stream);
     if (e == hipSuccess) e = launch_sum(jpart, moments_groups(c->grid), 1, sum, c->stream);
     if (e == hipSuccess && !slot.p) e = hipMemcpyAsync(value, sum, sizeof(double), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = slot.wait(c->stream);
+    if (e == hipSuccess) e = slot.wait();
     if (e == hipSuccess && slot.p) *value = *slot.p;
     return e == hipSuccess ? LBM_OK : fail_hip(e, "objective evaluation");
 }

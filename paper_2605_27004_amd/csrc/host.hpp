@@ -67,18 +67,22 @@ bool aligned256(const void *ptr);
 // whole process, allocated at the first use and kept: 16 of 32 KiB. Each belongs to one call at a
 // time, from its construction to its end, so calls on other threads, streams and devices never
 // share one. p is null when none is free or the totals are larger; the caller then copies.
+// A place is given back only once the stream has been waited for: by wait(), or, where a call ends
+// early because something failed, by the destructor, since a kernel enqueued before the failure may still
+// write to it. If that wait fails too, the place stays taken.
 class HostSlot {
 public:
-    explicit HostSlot(size_t bytes);
+    HostSlot(size_t bytes, hipStream_t stream);
     ~HostSlot();
     HostSlot(const HostSlot &) = delete;
     HostSlot &operator=(const HostSlot &) = delete;
-    // Wait for the stream. A failed wait leaves the place taken: a kernel may still write to it.
-    hipError_t wait(hipStream_t stream);
+    hipError_t wait();  // for the stream, whether there is a place or not
     double *p;
 
 private:
+    hipStream_t stream_;
     int at_;
+    bool waited_;
 };
 
 }  // namespace host
