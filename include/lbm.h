@@ -169,7 +169,10 @@ int lbm_init(lbm_ctx **out, const lbm_params *p, void *pop_a, void *pop_b, void 
 /* Advance by nsteps >= 0 steps of eq:LBE_BGK: fused kernels that gather the streamed populations,
  * form rho and s, build f^eq_i and relax with 1/tau. A launch makes one step, or, where that is
  * faster and bitwise the same, two steps (periodic three-dimensional grids in FP32 and FP64) or
- * several (D2Q9). Asynchronous. */
+ * several (D2Q9). Asynchronous.
+ * Recorded into a HIP graph, an even number of steps ends in the population buffer that it began
+ * in, so the graph can be replayed: each replay takes that many steps more (lbm_time counts the
+ * recorded call only). The same holds for lbm_batch_step. */
 int lbm_step(lbm_ctx *ctx, int64_t nsteps);
 
 /* Moments of the current state (eq:a0discrete_f, eq:a1discrete_f).

@@ -508,9 +508,11 @@ int run_steps(lbm_batch *b, int64_t nsteps)
 {
     const Plan &pl = b->pl;
     if (b->sched.mode == LBM_BATCH_STEPWISE) {
-        for (int64_t left = nsteps; left > 0;) {
-            const bool two = b->nsweep && !b->tile.steps && left >= 2;
-            const int many = b->tile.steps ? (int)std::min<int64_t>(left, b->tile.steps) : 0;
+        int64_t launches = launches_for(nsteps, b->tile.steps ? b->tile.steps : (b->nsweep ? 2 : 1), b->stream);
+        for (int64_t left = nsteps; left > 0; --launches) {
+            const int64_t k = steps_of_launch(left, launches);
+            const bool two = !b->tile.steps && k == 2;
+            const int many = b->tile.steps ? (int)k : 0;
             const hipError_t e =
                 many ? launch_batch_tile(pl.storage, pl.order, b->nsweep, (const BatchSweepRec *)b->dlaunch, b->ddom, b->dk64,
                                          b->dk32, b->pop[b->cur], b->pop[1 - b->cur], many, b->tile, b->stream)
@@ -521,7 +523,7 @@ int run_steps(lbm_batch *b, int64_t nsteps)
                                         2 * pl.pop_elems * pl.bytes <= 300000000, b->stream);
             if (e != hipSuccess) return fail_hip(e, "batch step launch");
             b->cur = 1 - b->cur;
-            left -= many ? many : (two ? 2 : 1);
+            left -= k;
         }
         return LBM_OK;
     }

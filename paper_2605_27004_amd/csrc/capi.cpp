@@ -95,6 +95,20 @@ hipError_t HostSlot::wait()
     return e;
 }
 
+// ---- launches of several steps ---------------------------------------------------------
+
+int64_t launches_for(int64_t n, int64_t most, hipStream_t stream)
+{
+    const int64_t fewest = n / most + (n % most != 0);
+    if (((fewest ^ n) & 1) == 0) return fewest;
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &s) != hipSuccess) {
+        (void)hipGetLastError();  // (the null stream beside another one that is being recorded)
+        return fewest;
+    }
+    return s == hipStreamCaptureStatusNone ? fewest : fewest + 1;  // fewest < n where their parities differ
+}
+
 // ---- lattice tables in canonical order -------------------------------------------------
 
 
@@ -385,18 +399,10 @@ using namespace lbm::host;
 
 namespace {
 
-// Steps the next launch takes when `left` >= 1 are to be taken: a tiled launch's share (the steps
-// spread evenly over the launches), the two of a sweep, or one.
-int64_t pass_steps(const lbm_ctx *c, int64_t left)
-{
-    if (c->tile.shape >= 0) {
-        const int64_t passes = (left + c->tile.steps - 1) / c->tile.steps;
-        return (left + passes - 1) / passes;
-    }
-    return c->sweep.tx && left >= 2 ? 2 : 1;
-}
+// Most steps of one launch: a tiled launch's, the two of a sweep, or one.
+int64_t most_steps(const lbm_ctx *c) { return c->tile.shape >= 0 ? c->tile.steps : (c->sweep.tx ? 2 : 1); }
 
-// One launch of k = pass_steps steps from src to dst.
+// One launch of k <= most_steps steps from src to dst.
 hipError_t launch_pass(const lbm_ctx *c, int64_t k, const void *src, void *dst)
 {
     if (k == 1)
@@ -412,8 +418,9 @@ hipError_t launch_pass(const lbm_ctx *c, int64_t k, const void *src, void *dst)
 // n >= 1 steps from src to dst through the context's population buffers (src may be neither of them).
 hipError_t advance(const lbm_ctx *c, const void *src, void *dst, int64_t n)
 {
-    for (int i = 0; n > 0; i ^= 1) {
-        const int64_t k = pass_steps(c, n);
+    int64_t left = launches_for(n, most_steps(c), c->stream);
+    for (int i = 0; n > 0; i ^= 1, --left) {
+        const int64_t k = steps_of_launch(n, left);
         void *out = k == n ? dst : c->pop[i];
         const hipError_t e = launch_pass(c, k, src, out);
         if (e != hipSuccess) return e;
@@ -426,8 +433,8 @@ hipError_t advance(const lbm_ctx *c, const void *src, void *dst, int64_t n)
 // n >= 0 steps from src, each state kept: state s (after s + 1 steps) at base + s stride bytes.
 hipError_t record(const lbm_ctx *c, const void *src, char *base, int64_t stride, int64_t n)
 {
-    while (n > 0) {
-        const int64_t k = c->tile.shape >= 0 ? pass_steps(c, n) : 1;
+    for (int64_t left = launches_for(n, c->tile.shape >= 0 ? c->tile.steps : 1, c->stream); n > 0; --left) {
+        const int64_t k = steps_of_launch(n, left);
         const hipError_t e = k == 1 ? launch_pass(c, 1, src, base)
                                     : launch_tile(c->p.storage, c->p.order, c->grid, c->k64, c->k32, c->links, c->gray,
                                                   src, base, (uint64_t)(stride / c->pr.bytes), c->tile, (int)k, c->stream);
@@ -585,8 +592,8 @@ int lbm_step(lbm_ctx *c, int64_t nsteps)
 {
     if (!c) return fail(LBM_ERR_ARG, "ctx is NULL");
     if (nsteps < 0) return fail(LBM_ERR_ARG, "nsteps must be >= 0");
-    while (nsteps > 0) {
-        const int64_t k = pass_steps(c, nsteps);
+    for (int64_t left = launches_for(nsteps, most_steps(c), c->stream); nsteps > 0; --left) {
+        const int64_t k = steps_of_launch(nsteps, left);
         const hipError_t e = launch_pass(c, k, c->pop[c->cur], c->pop[c->cur ^ 1]);
         if (e != hipSuccess) return fail_hip(e, "step kernel launch");
         c->cur ^= 1;

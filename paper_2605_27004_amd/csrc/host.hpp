@@ -61,6 +61,14 @@ Grid grid_of(int64_t nx, int64_t ny, int64_t nz, int q, int bytes);
 int64_t align256(int64_t b);
 bool aligned256(const void *ptr);
 
+// Launches for n steps of at most `most` each: the fewest. While the stream is being recorded into a graph
+// (and most > 1), as many as leave the state in the buffer that n launches of one step would, at most one
+// more: a graph of an even number of steps can then be replayed, each replay going on from the state that the
+// last one left.
+int64_t launches_for(int64_t n, int64_t most, hipStream_t stream);
+// Steps of the next launch when `left` steps are to be taken in `launches` of them.
+inline int64_t steps_of_launch(int64_t left, int64_t launches) { return (left + launches - 1) / launches; }
+
 // A place in pinned host memory, for the few totals that a call's last kernel writes and the call
 // then waits for: a read-out takes one synchronisation that way, where a copy to pageable memory
 // costs another 9 us (lbm_moments of a 64^2 grid 27.0 -> 18.7 us). The places come from one block for the
