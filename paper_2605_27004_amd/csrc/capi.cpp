@@ -556,7 +556,7 @@ int lbm_init(lbm_ctx **out, const lbm_params *p, void *pop_a, void *pop_b, void 
     const bool general = masked || grayed || c->k64.forced;
     if (p->lattice == LBM_D2Q9) {
         if (tile_serves(p->storage, grayed, masked || c->k64.forced))
-            c->tile = plan_tile(p->storage, c->grid, general);
+            c->tile = plan_tile(p->storage, c->grid, general, grayed);
     } else if (!general) {
         c->sweep = plan_sweep(p->lattice, p->storage, c->grid);
     }

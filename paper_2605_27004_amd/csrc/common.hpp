@@ -129,13 +129,13 @@ hipError_t launch_sweep(int lattice, int storage, int order, const Grid &g, cons
                         hipStream_t stream);
 
 // ---- several steps of a two-dimensional grid in one launch (tile.hip) ----
-// Which of the compiled tiles and how many steps a launch takes at most; shape -1: none (set by
-// the context for other lattices and for launches the caller has shaped).
+// Which of the compiled tiles and how many steps a launch takes at most; shape -1: none (other
+// lattices, launches the caller has shaped, and grids on which single steps are the faster way).
 struct TilePlan {
     int shape, steps;
 };
 bool tile_serves(int storage, bool gray, bool links_or_force);
-TilePlan plan_tile(int storage, const Grid &g, bool general);  // general: links, gray cells or a force
+TilePlan plan_tile(int storage, const Grid &g, bool general, bool gray);  // general: links, gray cells or a force
 // `steps` steps from src. every = 0: the last state to dst; else state s to element dst + s every.
 hipError_t launch_tile(int storage, int order, const Grid &g, const StepConsts<double> &k64,
                        const StepConsts<float> &k32, const uint32_t *links, const float *gray, const void *src,

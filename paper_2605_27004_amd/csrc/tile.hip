@@ -16,6 +16,9 @@
 // 4096^2 FP32 193.6 -> 90.6, 2816 x 2746 FP16 55.9 -> 35.5.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
+
 #include "cell.hpp"
 #include "common.hpp"
 
@@ -194,7 +197,8 @@ bool tile_serves(int storage, bool gray, bool links_or_force)
     return storage != kF16 || gray || !links_or_force;
 }
 
-// The tile and the steps per launch, from sweeps over both (us per step; k = steps per launch):
+// The tile and the steps per launch (shape -1: single steps), from sweeps over both (us per step; k =
+// steps per launch):
 //  * small grids: the fewest cells per work-group, and many steps, since latency bounds a step
 //    whatever the rim costs (64^2 FP64: 32 x 16 k 8 1.00, k 5 1.28, 64 x 16 k 8 1.40; 200 x 150 FP32:
 //    32 x 16 k 6 1.33, k 8 1.64, 64 x 16 k 7 1.48);
@@ -205,14 +209,42 @@ bool tile_serves(int storage, bool gray, bool links_or_force)
 //    k 5 54.0). FP64 takes 64 x 16, k 4, two of which share a compute unit's LDS (2816 x 2746: 75.5
 //    against 81.3 with 64 x 32), and so do 16-bit storage and a force with k 3 (FP16 gray 50.5 against
 //    59.9: its conversions take the VALU, and the larger tile's registers the waves).
-TilePlan plan_tile(int storage, const Grid &g, bool general)
+//
+// Against that plan stands the single step: a tile that the grid does not fill computes its idle columns and
+// rows all the same, so strips and rows a little longer than a tile may lose (us per step, single -> tiles:
+// 4,000,000 x 1 FP32 51 -> 422, 100,000 x 4 FP16 5.4 -> 11.5, 8 x 125,000 FP32 12 -> 33, 64 x 6000 BF16 with
+// a force 5.5 -> 8.7; but 24 x 40,000 FP64 22 -> 21, 20,000 x 30 FP32 8.7 -> 6.4). The times of both over
+// 55 grids of 1 x 8192 to 300,000 x 20 cells, plain, with gray cells and with a force, are within 20%
+// (80% of them) of
+//  * a launch of tiles: 6.5 us (32 x 16), 9 us (64 x 16) or, of the tile that has a compute unit to itself,
+//    5 us and most of a turn, and a turn of one tile per compute unit: steps x cells (the rows that
+//    drop out left out) x the time of a cell;
+//  * a single step: 3.9 us at least, or 2.8 us and the time of its cells.
+TilePlan plan_tile(int storage, const Grid &g, bool general, bool gray)
 {
-    if (g.n <= 8192) return TilePlan{0, 8};
-    if (g.n <= 100000) return TilePlan{0, 6};
-    if (g.n <= 400000) return TilePlan{2, 6};
-    if (storage == kF64) return TilePlan{1, 4};
-    if (storage == kF32) return TilePlan{2, general ? 4 : 5};
-    return general ? TilePlan{1, 3} : TilePlan{2, 5};
+    const bool f64 = storage == kF64, f32 = storage == kF32;
+    TilePlan p;
+    if (g.n <= 8192) p = TilePlan{0, 8};
+    else if (g.n <= 100000) p = TilePlan{0, 6};
+    else if (g.n <= 400000) p = TilePlan{2, 6};
+    else if (f64) p = TilePlan{1, 4};
+    else if (f32) p = TilePlan{2, general ? 4 : 5};
+    else p = general ? TilePlan{1, 3} : TilePlan{2, 5};
+
+    const TileShape &sh = kShapes[p.shape];
+    const int ow = sh.tw - 2 * (p.steps - 1), oh = sh.height() - 2 * (p.steps - 1);
+    const double tiles = (double)((g.nx + ow - 1) / ow) * (double)((g.ny + oh - 1) / oh), turns = tiles / 256.0;
+    const double cell_ns = f64   ? (gray ? 1.8 : (general ? 1.9 : 1.27))
+                           : f32 ? (gray ? 1.1 : (general ? 1.4 : 0.85))
+                                 : (gray ? 1.25 : (general ? 1.35 : 0.78));
+    const double turn_us = 1e-3 * cell_ns * p.steps * sh.tw * (sh.height() - p.steps + 1);
+    const double launch_us = p.shape == 2 ? 5.0 + turn_us * std::max(std::ceil(turns), turns + 0.75)
+                                          : (p.shape == 0 ? 6.5 : 9.0) + turn_us * turns;
+    const double cell_ps = f64 ? 20.0 : (f32 ? 10.0 : (general ? 7.3 : 5.8));
+    // (rows that the lane exchange serves are at the model's lower side, others at its upper side)
+    const double factor = g.nx % 64 == 0 && g.nx <= 256 ? 0.95 : 1.1;
+    const double single_us = std::max(3.9, factor * (2.8 + 1e-6 * cell_ps * g.n));
+    return launch_us / p.steps < single_us ? p : TilePlan{-1, 1};
 }
 
 hipError_t launch_tile(int storage, int order, const Grid &g, const StepConsts<double> &k64,

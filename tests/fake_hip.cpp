@@ -34,8 +34,8 @@ thread_local struct {
 // Arguments of 8 bytes or less that may be read, by kernel; at least the first two of every kernel.
 int readable(const std::string &name)
 {
-    if (name.find("k_tile<") != std::string::npos) return 8;
-    if (name.find("k_batch_tile<") != std::string::npos) return 7;
+    if (name.find("k_tile") != std::string::npos) return 8;
+    if (name.find("k_batch_tile") != std::string::npos) return 7;
     if (name.find("k_sum_partials") != std::string::npos) return 4;
     if (name.find("k_reduce_partials") != std::string::npos) return 3;
     return 2;
@@ -44,8 +44,8 @@ int readable(const std::string &name)
 // Bytes of argument i that a kernel takes as a 32-bit number.
 bool is_int(const std::string &name, int i)
 {
-    if (name.find("k_tile<") != std::string::npos) return i == 7;
-    if (name.find("k_batch_tile<") != std::string::npos) return i >= 5;
+    if (name.find("k_tile") != std::string::npos) return i == 7;
+    if (name.find("k_batch_tile") != std::string::npos) return i >= 5;
     if (name.find("k_sum_partials") != std::string::npos) return i == 1 || i == 2;
     if (name.find("k_reduce_partials") != std::string::npos) return i == 1;
     return false;
