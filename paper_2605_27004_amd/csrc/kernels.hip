@@ -1383,7 +1383,7 @@ hipError_t launch_step(int lattice, int storage, int order, const Grid &g, const
             const int mode = (flags & kLaunchStreamOnly) ? kStream
                              : gray ? kGray : ((links != nullptr || kc->forced) ? kLinks : kPlain);
             const StepShape sh = step_shape(mode, LAT, sizeof(S), g, block_x, flags);
-            const bool shaped = !(flags & kLaunchDefault);
+            const bool shaped = !(flags & kLaunchDefault);  // (lbm_init may set kLaunchXcdSlabs beside it)
             const dim3 block = sh.pull == kPullFlat ? dim3(256) : (sh.pull == kPullCompact && !shaped ? dim3(64, sh.rows) : dim3(block_x, block_y));
             const dim3 g3 = sh.pull == kPullFlat
                                 ? dim3(((uint32_t)g.nx * (uint32_t)g.ny + 255u) / 256u, 1u, (uint32_t)g.nz)

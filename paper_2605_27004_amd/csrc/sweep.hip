@@ -127,38 +127,48 @@ constexpr uint32_t kCus = 256;  // compute units of the MI355X; one work-group o
 
 // Tile widths and largest heights of the compiled sweeps (the LDS of a tile and its rim, and 1,024
 // lanes), and the measured time of one row of `tx` cells of one plane (us); a plane of a tile of h
-// rows takes the time of h + 1.
+// rows takes the time of h + 1, but low_us + h low_row_us at least: with few waves its latencies count.
 struct SweepTile {
     int lattice, storage, tx, tym;
-    double row_us;
+    double row_us, low_us, low_row_us;
 };
 constexpr SweepTile kTiles[] = {
-    {kD3Q19, kF32, 64, 13, 0.46},
-    {kD3Q19, kF64, 32, 16, 0.46},
-    {kD3Q19, kF64, 64, 7, 0.87},
-    {kD3Q27, kF32, 64, 9, 0.78},
-    {kD3Q27, kF64, 32, 10, 0.72},
+    {kD3Q19, kF32, 64, 13, 0.46, 2.0, 0.0},
+    {kD3Q19, kF64, 32, 16, 0.46, 1.65, 0.27},
+    {kD3Q19, kF64, 64, 7, 0.87, 0.0, 0.0},
+    {kD3Q27, kF32, 64, 9, 0.78, 0.0, 0.0},
+    {kD3Q27, kF64, 32, 10, 0.72, 2.7, 0.40},
 };
+
+// Bytes per us of single steps over grids of `both` bytes of populations: rows of 64 n cells 5.8 TB/s up to 90 MB
+// (6.0 to 6.3 at 40 MB, by where the buffers lie), other rows 5.4 TB/s where they are no whole cache lines and
+// the caches no longer hold the state.
+double single_rate(const Grid &g, int bytes, double both)
+{
+    if (g.nx % 64 == 0 && both <= 300e6) return both <= 90e6 ? 5.8e6 : 6.1e6;
+    return both > 300e6 && g.nx * bytes % 128 != 0 ? 5.4e6 : 6.3e6;
+}
 
 }  // namespace
 
 // The cut of a grid into tiles and segments, from the time that a cut takes: rounds of one
 // work-group per compute unit x planes (two more than the segment's, for the rim) x rows. Measured
-// over grids of 40 x 40 x 500 to 256^3, even and odd, it is right to 10% or so. Against it stands
-// the time of two single steps: 2 us a launch and the bytes at 6.3 TB/s, or 5.4 TB/s where rows are
-// no whole cache lines and the caches no longer hold the state. The line so lies near 100^3: below,
-// the work-groups are too few and their rims too large (us per step, single against sweep,
-// D3Q19 FP32: 48^3 5.7 / 6.1, 100^3 24.3 / 28.4, 150 x 101 x 75 28.5 / 29.8, 128 x 96 x 80 24.7 / 20.8,
-// 200 x 150 x 100 80.7 / 68.7, 250 x 190 x 130 175.3 / 120.6; D3Q27 FP32: 100^3 34.0 / 46.3, 128^3
-// 73.6 / 63.0; D3Q19 FP64: 77 x 85 x 60 22.2 / 23.9, 110 x 120 x 100 78.7 / 56.6).
+// over grids of 40 x 40 x 500 to 256^3, even and odd, it is right to 10% or so. Against it, with the
+// latencies of low tiles, stands the time of two single steps: 2 us a launch and the bytes. The line so
+// lies between 40 and 100 MB of populations in FP32 and near 80 MB in FP64 (D3Q19) or 200 MB (D3Q27): below, the
+// work-groups are too few and their rims too large (us per step, single against sweep, D3Q19 FP32: 48^3
+// 5.7 / 6.1, 64^3 7.2 to 8.3 / 7.2, 64 x 69 x 83 12.2 / 9.7, 100^3 24.3 / 28.4, 150 x 101 x 75 28.5 / 29.8, 128 x 96 x 80
+// 24.7 / 20.8, 200 x 150 x 100 80.7 / 68.7, 250 x 190 x 130 175.3 / 120.6; D3Q27 FP32: 100^3 34.0 / 46.3, 128^3
+// 73.6 / 63.0; D3Q19 FP64: 64 x 48 x 54 10.5 / 12.0, 64 x 64 x 52 12.4 / 13.6, 64^3 15.8 / 15.0, 77 x 85 x 60
+// 22.2 / 23.9, 110 x 120 x 100 78.7 / 56.6; D3Q27 FP64: 64^3 21.0 / 22.6, 64 x 99 x 60 29.0 / 31.1, 64 x 108 x 81
+// 43.5 / 38.9).
 SweepPlan plan_sweep(int lattice, int storage, const Grid &g)
 {
     SweepPlan best{0, 0, 0};
     const int bytes = storage == kF64 ? 8 : 4;
     const double q = lattice == kD3Q19 ? 19.0 : 27.0;
     const double both = 2.0 * q * bytes * g.n;  // bytes of a step
-    const double rate = both > 300e6 && g.nx * bytes % 128 != 0 ? 5.4e6 : 6.3e6;  // bytes per us
-    double best_us = 2.0 * (2.0 + both / rate) / 1.05;
+    double best_us = 1e300, low_us = 1e300;
     for (const SweepTile &t : kTiles) {
         if (t.lattice != lattice || t.storage != storage) continue;
         // D3Q19 FP64: rows of 32 cells where they are whole cache lines (256^3: 505 against 532 us),
@@ -169,15 +179,18 @@ SweepPlan plan_sweep(int lattice, int storage, const Grid &g)
             const int64_t tiles = tx * ((g.ny + ty - 1) / ty);
             for (int segs = 1; segs <= std::max(1, g.nz / 2) && segs <= 64; ++segs) {
                 const int64_t rounds = (tiles * segs + kCus - 1) / kCus;
-                const double us = 2.0 + (double)rounds * ((g.nz + segs - 1) / segs + 2) * (ty + 1) * t.row_us;
+                const double planes = (double)rounds * ((g.nz + segs - 1) / segs + 2);
+                const double us = 2.0 + planes * (ty + 1) * t.row_us;
                 if (us < best_us) {
                     best_us = us;
+                    low_us = 2.0 + planes * std::max((ty + 1) * t.row_us, t.low_us + ty * t.low_row_us);
                     best = SweepPlan{t.tx, ty, segs};
                 }
             }
         }
     }
-    return best;
+    const double single_us = 2.0 * (2.0 + both / single_rate(g, bytes, both));
+    return low_us < single_us / 1.05 ? best : SweepPlan{0, 0, 0};
 }
 
 hipError_t launch_sweep(int lattice, int storage, int order, const Grid &g, const StepConsts<double> &k64,
