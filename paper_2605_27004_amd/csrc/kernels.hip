@@ -1330,12 +1330,14 @@ struct StepShape {
 //    its L2 put the lines together. Boxes with non-temporal stores -> runs with cached ones:
 //    FP16 129 x 100 x 90 26.3 -> 16.3, 250 x 190 x 130 104.5 -> 91.0; FP32 gray 129 x 100 x 90
 //    45.0 -> 29.3, 250 x 190 x 130 232.8 -> 179.2; D3Q27 BF16 155 x 197 x 157 128.2 -> 115.7; masked
-//    D3Q27 FP32 129 x 100 x 90 67.6 -> 50.8, FP16 45.4 -> 29.4. Runs with non-temporal stores are no
-//    better than boxes there (FP16 129 x 100 x 90 21.9). Rows of whole lines (96 cells in FP32) take
-//    them on large grids all the same, as above.
-//    Gray grids of 12 to 32 MB whose boxes leave few lanes idle keep the boxes: 57 x 47 x 77 FP16 6.62 against
-//    7.05, FP32 9.03 against 9.63 (62 x 80 x 80 10.26 and 10.43; without gray cells 6.48 against 6.26; smaller,
-//    60 x 30 x 30, 4.46 against 3.98; larger, 120 x 60 x 60, 10.76 against 9.89).
+//    D3Q27 FP32 129 x 100 x 90 67.6 -> 50.8, FP16 45.4 -> 29.4. Over 4,200 grids of all lattices, storages
+//    and walls, runs with cached stores take 0.88 of the boxes' time at 2 to 8 MB (non-temporal: 0.94), 0.75 at
+//    40 to 250 MB (0.92), 0.70 (16-bit) to 0.88 (FP64) from 500 MB on (0.81, 0.93). Non-temporal stores win
+//     - at 12 to 20 MB, near the 32 MB of the XCDs' L2s, which then hold what is read instead (16-bit 0.86
+//       against 0.91, FP32 0.90 against 0.93; FP64 the other way round, 0.825 and 0.805);
+//     - past 300 MB on rows that are a multiple of 64 bytes, which leave no parts of a cache line's halves (FP64
+//       0.98 against 1.03 to 1.06, FP32 0.98 and 1.00, 16-bit 0.91 and 0.94), and up to 500 MB in all of FP64 (0.96
+//       against 0.99) and on rows of a multiple of 32 bytes (FP32 0.93 against 0.97).
 //  * Longer rows of a multiple of 64 cells, and the links step on any multiple: boxes, shifted
 //    loads, non-temporal stores. In the links step the tiles of a row share an XCD: its shifted
 //    and bounce-back pulls read lines that they share, which the L2 then serves once (512^3
@@ -1356,12 +1358,11 @@ StepShape step_shape(int mode, int lat, size_t bytes, const Grid &g, int block_x
     const double q = lat == kD2Q9 ? 9 : (lat == kD3Q19 ? 19 : 27);
     const double both = 2.0 * q * (double)bytes * g.n;
     const bool near = both >= 80e6 && both <= 400e6;
-    const int32_t lanes = (g.nx + 63) / 64 * 64;
-    const bool boxes = mode == kGray && both >= 12e6 && both <= 32e6 && 20ll * g.nx >= 17ll * lanes;
-    if (!shaped && g.nx % 64 != 0 && boxes) return StepShape{kPullShifted, false, 1u, 1u};
     if (!shaped && g.nx % 64 != 0) {
-        const bool whole_lines = g.nx * bytes % 128 == 0;
-        return StepShape{kPullFlat, !whole_lines || both <= 400e6, 16u, 1u};
+        const size_t row = (size_t)g.nx * bytes;
+        const bool l2 = bytes < 8 && both >= 12e6 && both <= 20e6;
+        const bool past = both > 300e6 && (row % 64 == 0 || (both <= 500e6 && (bytes == 8 || row % 32 == 0)));
+        return StepShape{kPullFlat, !l2 && !past, 16u, 1u};
     }
     if (mode != kLinks && !(flags & kLaunchShiftedPull) && g.nx % 64 == 0 && block_x == g.nx)
         return StepShape{kPullRows, !shaped && near, 1u, 1u};
