@@ -17,7 +17,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <cmath>
 
 #include "cell.hpp"
 #include "common.hpp"
@@ -238,11 +237,13 @@ TilePlan plan_tile(int storage, const Grid &g, bool general, bool gray)
                            : f32 ? (gray ? 1.1 : (general ? 1.4 : 0.85))
                                  : (gray ? 1.25 : (general ? 1.35 : 0.78));
     const double turn_us = 1e-3 * cell_ns * p.steps * sh.tw * (sh.height() - p.steps + 1);
-    const double launch_us = p.shape == 2 ? 5.0 + turn_us * std::max(std::ceil(turns), turns + 0.75)
+    const double launch_us = p.shape == 2 ? 5.0 + turn_us * std::max(1.0, turns + 0.75)
                                           : (p.shape == 0 ? 6.5 : 9.0) + turn_us * turns;
-    const double cell_ps = f64 ? 20.0 : (f32 ? 10.0 : (general ? 7.3 : 5.8));
+    // (past the Infinity Cache a quarter more in FP64, a fifth in FP32)
+    const bool large = 18.0 * (f64 ? 8 : (f32 ? 4 : 2)) * g.n > 300e6;
+    const double cell_ps = f64 ? (large ? 25.0 : 20.0) : (f32 ? (large ? 12.0 : 10.0) : (general ? 7.3 : 5.8));
     // (rows that the lane exchange serves are at the model's lower side, others at its upper side)
-    const double factor = g.nx % 64 == 0 && g.nx <= 256 ? 0.95 : 1.1;
+    const double factor = g.nx % 64 == 0 && g.nx <= 256 ? (f64 || f32 ? 1.0 : 0.95) : 1.1;
     const double single_us = std::max(3.9, factor * (2.8 + 1e-6 * cell_ps * g.n));
     return launch_us / p.steps < single_us ? p : TilePlan{-1, 1};
 }
