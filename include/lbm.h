@@ -162,7 +162,10 @@ int64_t lbm_scratch_bytes(const lbm_params *p);
  *                 float [N], the gray fraction in [0, 1]; NULL otherwise. Read during this
  *                 call's device work only.
  *   stream:       hipStream_t for all work of this context.
- * On success *out receives the context (free with lbm_destroy). Asynchronous. */
+ * On success *out receives the context (free with lbm_destroy). Asynchronous, but for masked
+ * three-dimensional grids in FP64 or FP32 with nx a multiple of 64 and 64 MB of populations or more: what
+ * suits the mask decides how their rows are stored, and the call waits for the stream to learn it
+ * (not while the stream is being recorded into a graph). */
 int lbm_init(lbm_ctx **out, const lbm_params *p, void *pop_a, void *pop_b, void *scratch, const double *rho0,
              const double *s0, const void *mask, void *stream);
 

@@ -101,12 +101,15 @@ int64_t launches_for(int64_t n, int64_t most, hipStream_t stream)
 {
     const int64_t fewest = n / most + (n % most != 0);
     if (((fewest ^ n) & 1) == 0) return fewest;
+    return recording(stream) ? fewest + 1 : fewest;  // fewest < n where their parities differ
+}
+
+bool recording(hipStream_t stream)
+{
     hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &s) != hipSuccess) {
-        (void)hipGetLastError();  // (the null stream beside another one that is being recorded)
-        return fewest;
-    }
-    return s == hipStreamCaptureStatusNone ? fewest : fewest + 1;  // fewest < n where their parities differ
+    if (hipStreamIsCapturing(stream, &s) == hipSuccess) return s != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();  // (the null stream beside another one that is being recorded)
+    return false;
 }
 
 // ---- lattice tables in canonical order -------------------------------------------------
@@ -360,22 +363,29 @@ template <typename C> StepConsts<C> consts_for(const lbm_params &p, const Prepar
     return k;
 }
 
-// Whether a masked grid stores its rows compact (RowRec). The index fits in the link words' share of the
-// scratch: 8 ceil(nx / 30) + 4 + 2 nx bytes for a row, against 4 nx. Us per step, link words -> compact
-// rows; ellipsoids that leave 60% fluid, and two plates with fluid between:
-//  * FP64, any size: D3Q19 128^3 102.5 -> 78.0 and 108.0 -> 105.9, 256 x 128 x 128 201 -> 140 and 213.6 ->
-//    209.4, D3Q27 64^3 22.5 -> 20.2 and 23.2 -> 22.9, 128 x 8 x 8 6.5 -> 6.3 and 6.3 -> 6.1. Random
-//    single cells gain nothing until they are many (D3Q19 128^3 with 5% solid 110.8 -> 113.3).
-//  * FP32 from 64 MB on and rows of 128 cells: D3Q27 256^3 588 -> 441 and 588 -> 592, 512^3 4,807 -> 3,347,
-//    128^3 76 -> 64.6 and 75.7 -> 78.6, D3Q19 128^3 53.9 -> 45.7 and 53.9 -> 54.8, 512 x 128 x 128 210 -> 155
-//    and 211 -> 212, 128 x 64 x 64 16.9 -> 15.4; a row index, read before anything else can start, costs more on smaller grids: 128 x 32 x 32
-//    5.5 -> 6.4, 64^3 10.0 -> 10.4 and 8.8 -> 10.2.
-//  * Never for 16-bit storage, where the lookups cost as much as the solid cells' bytes: D3Q27 FP16 256^3
-//    319 -> 304 and 324 -> 329, but 384 -> 471 with 10% random single cells.
+// Whether a masked grid may store its rows compact (RowRec); whether it does, the mask decides (compact_pays).
+// The index fits in the link words' share of the scratch: 8 ceil(nx / 30) + 4 + 2 nx bytes for a row, against
+// 4 nx. Not below 64 MB of populations and, in FP32, not on rows of 64 cells: the row index, read before
+// anything else can start, costs more than it gives there (D3Q19 FP64 64 x 24 x 24 1.05 to 1.13 of the time
+// over all masks, FP32 64^3 10.0 -> 10.4 us). Never for 16-bit storage, where the lookups cost as much as the solid
+// cells' bytes (D3Q27 FP16 256^3 319 -> 304 and 324 -> 329 us, but 384 -> 471 with 10% random single cells).
 bool compact_rows(const lbm_params &p, int q, int bytes, uint32_t n)
 {
     if (p.lattice == LBM_D2Q9 || p.nx % 64 != 0 || p.nx > (int64_t)kMaxCompactRow) return false;
-    return bytes == 8 || (bytes == 4 && p.nx >= 128 && 2.0 * q * bytes * n >= 64e6);
+    return 2.0 * q * bytes * n >= 64e6 && (bytes == 8 || (bytes == 4 && p.nx >= 128));
+}
+
+// Whether compact rows are the faster way for a mask: `solid` of the n cells, in `runs` runs along x. What
+// they save grows with the solid cells; what they cost, with the places where neighbouring rows fall out of
+// step. Us per step, link words -> compact rows: D3Q19 FP32 128^3 no solid cell 53.4 -> 54.8, 3% in one sphere
+// 53.2 -> 54.5, 5% (10%) of random cells 55.8 -> 61.0 (56.6 -> 62.5), 21% in ellipsoids 0.98 of the time, 40%
+// 53.4 -> 45.6, 22% (30%) random 1.04 (57.5 -> 52.9); 256^3 22% outside a pipe 0.89, 20% in ellipsoids 0.90, 40%
+// 416 -> 309, 10% (22%) random 454 -> 473 (456 -> 430); D3Q27 256^3 40% 590 -> 443; FP64 D3Q19 128^3 none 108 -> 107, 12% random 0.92 to 0.98,
+// 40% in ellipsoids 102 -> 80; 64^3 12% random 1.07, 30% random 0.88, 31% in ellipsoids 0.99.
+bool compact_pays(int bytes, double both, double n, double solid, double runs)
+{
+    const double least = bytes == 8 ? (both >= 200e6 ? 0.07 : 0.2) : (both >= 500e6 ? 0.14 : 0.2);
+    return (solid - 0.4 * runs) / n >= least;
 }
 
 // Scratch layout: [link words or row index, 4 bytes per cell, when masked][partials][totals],
@@ -398,6 +408,26 @@ template StepConsts<double> consts_for<double>(const lbm_params &, const Prepare
 using namespace lbm::host;
 
 namespace {
+
+// compact_pays of a mask in device memory: the two numbers are counted there and waited for. A stream that
+// is being recorded cannot be waited for: link words serve every mask.
+hipError_t mask_pays(const lbm_ctx *c, const uint8_t *mask, bool &compact)
+{
+    compact = false;
+    if (recording(c->stream)) return hipSuccess;
+    const uint32_t nb = moments_groups(c->grid);  // (the partials hold kPartials doubles for each)
+    double h[2];
+    HostSlot slot(sizeof h, c->stream);
+    double *out = slot.p ? slot.p : c->partials + kPartials * (size_t)nb;
+    hipError_t e = launch_mask_stats(c->grid, mask, c->partials, nb, out, c->stream);
+    if (e == hipSuccess && !slot.p) e = hipMemcpyAsync(h, out, sizeof h, hipMemcpyDeviceToHost, c->stream);
+    if (e == hipSuccess) e = slot.wait();
+    if (e != hipSuccess) return e;
+    if (slot.p) std::memcpy(h, slot.p, sizeof h);
+    const double n = (double)c->grid.n;
+    compact = compact_pays(c->pr.bytes, 2.0 * c->pr.q * c->pr.bytes * n, n, h[0], h[1]);
+    return hipSuccess;
+}
 
 // Most steps of one launch: a tiled launch's, the two of a sweep, or one.
 int64_t most_steps(const lbm_ctx *c) { return c->tile.shape >= 0 ? c->tile.steps : (c->sweep.tx ? 2 : 1); }
@@ -526,10 +556,18 @@ int lbm_init(lbm_ctx **out, const lbm_params *p, void *pop_a, void *pop_b, void 
     c->pop[1] = pop_b;
     c->cur = 0;
     c->links = masked ? (uint32_t *)scratch : nullptr;
-    if (masked && compact_rows(*p, pr.q, pr.bytes, pr.n)) c->grid.nrec = ((uint32_t)p->nx + kRecCells - 1u) / kRecCells;
     c->gray = grayed ? (float *)scratch : nullptr;
     c->partials = (double *)((char *)scratch + links_bytes(*p, pr.n));
     c->stream = (hipStream_t)stream;
+    if (masked && compact_rows(*p, pr.q, pr.bytes, pr.n)) {
+        bool compact = false;
+        const hipError_t e = mask_pays(c, (const uint8_t *)mask, compact);
+        if (e != hipSuccess) {
+            delete c;
+            return fail_hip(e, "mask statistics");
+        }
+        if (compact) c->grid.nrec = ((uint32_t)p->nx + kRecCells - 1u) / kRecCells;
+    }
     c->t = 0;
     // Work-groups span whole x rows where they fit (up to 256 cells), so the boundary cache
     // line of every x-shifted pull is shared by waves of the same work-group; the rest of the

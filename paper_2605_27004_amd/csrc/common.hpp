@@ -103,6 +103,11 @@ __host__ __device__ inline RowIndex row_index(const Grid &g, const uint32_t *scr
 // index of a grid of compact rows (g.nrec != 0), or null for a grid without solid cells.
 hipError_t launch_links(int lattice, const Grid &g, const uint8_t *mask, uint32_t *links, hipStream_t stream);
 
+// out[0]: solid cells of the mask, out[1]: runs of solid cells along x (rows of a multiple of 64 cells);
+// part: 2 nblocks doubles.
+hipError_t launch_mask_stats(const Grid &g, const uint8_t *mask, double *part, uint32_t nblocks, double *out,
+                             hipStream_t stream);
+
 hipError_t launch_init(int lattice, int storage, int order, const Grid &g, const StepConsts<double> &k,
                        const double *rho, const double *s, const uint32_t *links, void *dst, hipStream_t stream);
 

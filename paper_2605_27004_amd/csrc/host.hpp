@@ -61,6 +61,9 @@ Grid grid_of(int64_t nx, int64_t ny, int64_t nz, int q, int bytes);
 int64_t align256(int64_t b);
 bool aligned256(const void *ptr);
 
+// Whether the stream is being recorded into a graph.
+bool recording(hipStream_t stream);
+
 // Launches for n steps of at most `most` each: the fewest. While the stream is being recorded into a graph
 // (and most > 1), as many as leave the state in the buffer that n launches of one step would, at most one
 // more: a graph of an even number of steps can then be replayed, each replay going on from the state that the

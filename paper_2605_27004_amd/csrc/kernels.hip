@@ -401,6 +401,29 @@ __global__ __launch_bounds__(256) void k_links(const uint8_t *__restrict__ mask,
     links[c.own] = w;
 }
 
+// Solid cells of a mask and runs of them along x (periodic rows), partial sums of both per work-group. Rows
+// are a multiple of 64 cells.
+__global__ __launch_bounds__(256) void k_mask_stats(const uint8_t *__restrict__ mask, double *__restrict__ part,
+                                                    const uint32_t nx, const uint32_t n)
+{
+    __shared__ uint32_t red[2][256];
+    uint32_t solid = 0u, runs = 0u;
+    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n; i += gridDim.x * 256u) {
+        if (mask[i] == 0) continue;
+        ++solid;
+        if (mask[i % nx == 0u ? i + nx - 1u : i - 1u] == 0) ++runs;
+    }
+    red[0][threadIdx.x] = solid;
+    red[1][threadIdx.x] = runs;
+    __syncthreads();
+    for (uint32_t h = 128u; h > 0u; h >>= 1) {
+        if (threadIdx.x < h)
+            for (int e = 0; e < 2; ++e) red[e][threadIdx.x] += red[e][threadIdx.x + h];
+        __syncthreads();
+    }
+    if (threadIdx.x < 2u) part[2u * blockIdx.x + threadIdx.x] = (double)red[threadIdx.x][0];
+}
+
 // The row index (RowRec) from a uint8 solid mask: one wave per row.
 __global__ __launch_bounds__(256) void k_row_index(const uint8_t *__restrict__ mask, RowRec *__restrict__ rec,
                                                    uint32_t *__restrict__ count, uint16_t *__restrict__ code, const Grid g)
@@ -1258,6 +1281,14 @@ hipError_t launch_links(int lattice, const Grid &g, const uint8_t *mask, uint32_
         hipLaunchKernelGGL((k_links<LAT>), grid, block, 0, stream, mask, links, g);
         return hipGetLastError();
     });
+}
+
+hipError_t launch_mask_stats(const Grid &g, const uint8_t *mask, double *part, uint32_t nblocks, double *out,
+                             hipStream_t stream)
+{
+    hipLaunchKernelGGL(k_mask_stats, dim3(nblocks), dim3(256), 0, stream, mask, part, (uint32_t)g.nx, g.n);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? launch_sum(part, nblocks, 2, out, stream) : e;
 }
 
 hipError_t launch_init(int lattice, int storage, int order, const Grid &g, const StepConsts<double> &k,

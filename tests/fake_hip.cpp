@@ -24,6 +24,8 @@ std::vector<Launch> g_log;
 std::string g_fail;      // launches of kernels whose name contains this fail
 int g_fail_after = 0;    // ... after this many good ones
 bool g_capturing = false;
+std::vector<double> g_result;                // what the next sums over work-groups give
+std::vector<std::pair<char *, size_t>> g_host;  // pinned host memory
 hipError_t g_last = hipSuccess;
 thread_local struct {
     dim3 grid, block;
@@ -69,6 +71,7 @@ void fake_fail(const char *name, int after)
     g_fail = name ? name : "";
     g_fail_after = after;
 }
+void fake_result(const double *v, int n) { g_result.assign(v, v + n); }
 int fake_count() { return (int)g_log.size(); }
 const char *fake_name(int i) { return g_log[(size_t)i].name.c_str(); }
 uint64_t fake_grid(int i) { return g_log[(size_t)i].grid; }
@@ -115,6 +118,12 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, si
     std::memset(l.arg, 0, sizeof l.arg);
     for (int i = 0; i < readable(l.name); ++i) std::memcpy(&l.arg[i], args[i], is_int(l.name, i) ? 4 : 8);
     g_log.push_back(l);
+    if (!g_result.empty() && l.name.find("k_sum_partials") != std::string::npos) {
+        for (const auto &h : g_host)
+            if (l.arg[3] >= (uint64_t)h.first && l.arg[3] < (uint64_t)h.first + h.second)
+                std::memcpy((void *)l.arg[3], g_result.data(), 8 * g_result.size());
+        g_result.clear();
+    }
     return hipSuccess;
 }
 hipError_t hipLaunchCooperativeKernel(const void *f, dim3 grid, dim3 block, void **args, unsigned shared, hipStream_t stream)
@@ -152,6 +161,7 @@ hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int)
 hipError_t hipHostMalloc(void **p, size_t n, unsigned)
 {
     *p = std::calloc(1, n);
+    g_host.emplace_back((char *)*p, n);
     return hipSuccess;
 }
 hipError_t hipMemcpy(void *dst, const void *, size_t n, hipMemcpyKind k)
