@@ -190,7 +190,9 @@ hipError_t run_tile(const Grid &g, const StepConsts<typename Conv<S>::C> &k, con
 // FP16 with a solid mask or a force (and no gray cells) stays with single steps. The compiler turns
 // a multiply-add and its conversion to FP16 into one instruction that rounds once (v_fma_mixlo_f16)
 // where no branch lies between the two; in that mode the single-step kernel gets it for some of the
-// directions and this one for none, so their results differ in the last bit now and then.
+// directions and this one for none, so their results differ in the last bit now and then. Without walls
+// and with gray cells both kernels get it for all nine, in every tile, pull and order; whether a compiler
+// does so is read from the built code in tests/test_host_fp16_rounding.py. Nothing of the kind exists for BF16.
 bool tile_serves(int storage, bool gray, bool links_or_force)
 {
     return storage != kF16 || gray || !links_or_force;
