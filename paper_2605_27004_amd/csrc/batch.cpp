@@ -173,6 +173,8 @@ struct lbm_batch {
     uint32_t nlaunch;        // tiles in the launch order
     uint32_t nsweep;         // records of the two-step launch in dlaunch's place (0: single steps only)
     BatchTilePlan tile;      // steps = 0, or the records are for launches of several steps
+    bool planned;            // `sweep` and `planned_tile` hold what domain-major stepwise schedules take
+    BatchTilePlan planned_tile;
     uint32_t nwg;            // persistent work-groups
     uint32_t max_chunks;     // largest items-per-domain count of the persistent lists
     // host copies of the schedule (kept alive across the uploads)
@@ -255,66 +257,76 @@ void build_launch_order(lbm_batch *b, bool xcd)
 // D3Q27 FP32 100 of 16 to 64 222 / 201, 119 of 12 to 42 89.1 / 89.6, 128 of 10 to 40 81.5 / 84.1, FP64 165 / 155).
 std::vector<BatchSweepRec> plan_sweeps(const Plan &pl, int cu_count)
 {
-    std::vector<BatchSweepRec> best;
     const int cols = batch_sweep_columns(pl.lattice, pl.storage);
-    if (cols == 0) return best;
+    if (cols == 0) return {};
     double bytes = 0.0;
     for (const BatchDomain &d : pl.dom) {
-        if ((int64_t)d.g.nx * std::min(d.g.ny, 4) > cols) return best;
+        if ((int64_t)d.g.nx * std::min(d.g.ny, 4) > cols) return {};
         bytes += 2.0 * pl.q * pl.bytes * d.cells;
     }
     const double row_us = 0.42 * (pl.q / 19.0) * (pl.bytes == 8 ? 1.72 : 1.0);
     const double full = 0.325 * ((cols + 63) / 64);
+    // a domain's tiles in y, its runs of z-planes, and the time of one plane of a tile
+    struct Cut {
+        int rows, tiles, segs;
+        double plane_us;
+    };
+    const auto cut = [&](const Grid &g, int len) {
+        Cut c;
+        const bool whole = (int64_t)g.nx * g.ny <= cols;
+        const int most_rows = cols / g.nx - 2;  // (a tile that is not whole)
+        const int tiles = whole ? 1 : (g.ny + most_rows - 1) / most_rows;
+        c.rows = whole ? g.ny : (g.ny + tiles - 1) / tiles;
+        c.tiles = (g.ny + c.rows - 1) / c.rows;
+        c.segs = (g.nz + len - 1) / len;
+        const int waves = (g.nx * (whole ? c.rows : c.rows + 2) + 63) / 64;
+        c.plane_us = (0.72 * waves + full) * row_us;
+        return c;
+    };
     double best_us = 2.0 * (2.0 + bytes / 6.1e6) / 1.03;
+    int best_len = 0;
     for (int len : {64, 48, 32, 24, 16, 12, 8, 6, 4}) {
-        std::vector<std::pair<double, BatchSweepRec>> jobs;
         double total = 0.0, most = 0.0;
-        for (size_t i = 0; i < pl.dom.size(); ++i) {
-            const Grid &g = pl.dom[i].g;
-            const bool whole = (int64_t)g.nx * g.ny <= cols;
-            const int tiles = whole ? 1 : (g.ny + cols / g.nx - 3) / (cols / g.nx - 2);
-            const int rows = whole ? g.ny : (g.ny + tiles - 1) / tiles;
-            const int segs = (g.nz + len - 1) / len;
-            for (int s = 0; s < segs; ++s)
-                for (int t = 0; t < tiles; ++t) {
-                    const int y0 = t * rows;
-                    if (y0 >= g.ny) break;
-                    const BatchSweepRec r{(uint32_t)i, y0, rows, (int32_t)((int64_t)g.nz * s / segs),
-                                          (int32_t)((int64_t)g.nz * (s + 1) / segs), 0u};
-                    const int waves = (g.nx * (whole ? rows : rows + 2) + 63) / 64;
-                    const double us = (r.z1 - r.z0 + 2) * (0.72 * waves + full) * row_us;
-                    total += us;
-                    most = std::max(most, us);
-                    jobs.emplace_back(us, r);
-                }
+        int64_t count = 0;
+        for (const BatchDomain &d : pl.dom) {
+            const Cut c = cut(d.g, len);
+            total += c.tiles * (d.g.nz + 2.0 * c.segs) * c.plane_us;
+            most = std::max(most, ((d.g.nz + c.segs - 1) / c.segs + 2) * c.plane_us);
+            count += (int64_t)c.tiles * c.segs;
         }
         const double us = 3.0 + std::max(total / cu_count + 0.3 * most, most);
-        if (us >= best_us || jobs.size() > 2 * pl.tiles.size()) continue;
+        if (us >= best_us || count > 2 * (int64_t)pl.tiles.size()) continue;
         best_us = us;
-        std::stable_sort(jobs.begin(), jobs.end(), [](const auto &a, const auto &b) { return a.first > b.first; });
-        best.clear();
-        for (const auto &j : jobs) best.push_back(j.second);
+        best_len = len;
     }
+    if (!best_len) return {};
+    std::vector<std::pair<double, BatchSweepRec>> jobs;
+    for (size_t i = 0; i < pl.dom.size(); ++i) {
+        const Grid &g = pl.dom[i].g;
+        const Cut c = cut(g, best_len);
+        for (int s = 0; s < c.segs; ++s)
+            for (int t = 0; t < c.tiles; ++t) {
+                const BatchSweepRec r{(uint32_t)i, t * c.rows, c.rows, (int32_t)((int64_t)g.nz * s / c.segs),
+                                      (int32_t)((int64_t)g.nz * (s + 1) / c.segs), 0u};
+                jobs.emplace_back((r.z1 - r.z0 + 2) * c.plane_us, r);
+            }
+    }
+    std::stable_sort(jobs.begin(), jobs.end(), [](const auto &a, const auto &b) { return a.first > b.first; });
+    std::vector<BatchSweepRec> best;
+    best.reserve(jobs.size());
+    for (const auto &j : jobs) best.push_back(j.second);
     return best;
 }
 
-// The records of the launch of several two-dimensional steps for a plan, empty where a domain's rows
-// do not fit.
-std::vector<BatchSweepRec> tile_records(const Plan &pl, const BatchTilePlan &p)
+// Rows of a plane that one work-group of the launch of several two-dimensional steps takes (without its rim): all of
+// them where the plane fits; 0 where not even one fits.
+int tile_rows(const Grid &g, const BatchTilePlan &p)
 {
-    std::vector<BatchSweepRec> out;
-    for (size_t i = 0; i < pl.dom.size(); ++i) {
-        const Grid &g = pl.dom[i].g;
-        if ((int64_t)g.nx * g.ny <= p.lanes) {
-            out.push_back(BatchSweepRec{(uint32_t)i, 0, g.ny, 0, 1, 0u});
-            continue;
-        }
-        const int fit = p.lanes / g.nx - 2 * (p.steps - 1);
-        if (fit < 1) return {};
-        const int tiles = (g.ny + fit - 1) / fit, rows = (g.ny + tiles - 1) / tiles;
-        for (int y0 = 0; y0 < g.ny; y0 += rows) out.push_back(BatchSweepRec{(uint32_t)i, y0, rows, 0, 1, 0u});
-    }
-    return out;
+    if ((int64_t)g.nx * g.ny <= p.lanes) return g.ny;
+    const int fit = p.lanes / g.nx - 2 * (p.steps - 1);
+    if (fit < 1) return 0;
+    const int tiles = (g.ny + fit - 1) / fit;
+    return (g.ny + tiles - 1) / tiles;
 }
 
 // Steps per launch and lanes for a batch of planes: the least time by a model of what was measured. A
@@ -337,15 +349,28 @@ BatchTilePlan plan_tiles(const Plan &pl, int cu_count, std::vector<BatchSweepRec
     for (int lanes : {512, 1024})
         for (int steps : {2, 3, 4, 5, 6, 8, 12, 16}) {
             const BatchTilePlan p{steps, lanes};
-            std::vector<BatchSweepRec> r = tile_records(pl, p);
-            if (r.empty() || r.size() > 2 * pl.tiles.size()) continue;
-            const double turns = (double)r.size() * lanes / 1024.0 / cu_count;
+            int64_t count = 0;
+            for (const BatchDomain &d : pl.dom) {
+                const int rows = tile_rows(d.g, p);
+                if (!rows) {
+                    count = 0;
+                    break;
+                }
+                count += (d.g.ny + rows - 1) / rows;
+            }
+            if (!count || count > 2 * (int64_t)pl.tiles.size()) continue;
+            const double turns = (double)count * lanes / 1024.0 / cu_count;
             const double step = std::max(lanes == 512 ? 0.70 : 0.93, (turns + 0.3) * (pl.bytes == 8 ? 1.5 : 1.0));
-            const double us = (2.2 + steps * step + 0.4 * ((double)r.size() * lanes + cells) / per_us) / steps;
+            const double us = (2.2 + steps * step + 0.4 * ((double)count * lanes + cells) / per_us) / steps;
             if (us >= best_us) continue;
             best_us = us;
             best = p;
-            recs = std::move(r);
+        }
+    if (best.steps)
+        for (size_t i = 0; i < pl.dom.size(); ++i) {
+            const Grid &g = pl.dom[i].g;
+            const int rows = tile_rows(g, best);
+            for (int y0 = 0; y0 < g.ny; y0 += rows) recs.push_back(BatchSweepRec{(uint32_t)i, y0, rows, 0, 1, 0u});
         }
     return best;
 }
@@ -473,11 +498,13 @@ int apply_schedule(lbm_batch *b, const lbm_batch_schedule &s)
     if (s.xcd_group != 0 && s.xcd_group != 1) return fail(LBM_ERR_ARG, "xcd_group must be 0 or 1");
     if (s.mode == LBM_BATCH_STEPWISE) {
         build_launch_order(b, s.xcd_group != 0);
-        b->sweep.clear();
-        b->tile = BatchTilePlan{0, 0};
-        if (!s.xcd_group) b->tile = plan_tiles(b->pl, b->cu_count, b->sweep);
-        if (!s.xcd_group && !b->tile.steps) b->sweep = plan_sweeps(b->pl, b->cu_count);
-        b->nsweep = (uint32_t)b->sweep.size();
+        if (!s.xcd_group && !b->planned) {  // (the domains alone decide: once for a batch)
+            b->planned_tile = plan_tiles(b->pl, b->cu_count, b->sweep);
+            if (!b->planned_tile.steps) b->sweep = plan_sweeps(b->pl, b->cu_count);
+            b->planned = true;
+        }
+        b->tile = s.xcd_group ? BatchTilePlan{0, 0} : b->planned_tile;
+        b->nsweep = s.xcd_group ? 0u : (uint32_t)b->sweep.size();
         // the records take the place of the launch order, which is then the natural one (dtiles)
         const int rc = b->nsweep
                            ? upload(b, b->dlaunch, b->sweep.data(), b->sweep.size() * sizeof(BatchSweepRec))

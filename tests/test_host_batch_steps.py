@@ -20,3 +20,34 @@ for n in (1, 2, 1, 5):
     assert len(one) == len(again) == 1 and "k_batch_step" in one[0] and one == again
     assert len(two) == 1 and kernel in two[0]
     assert len(five) <= 3 and kernel in five[0]
+
+
+def test_planning_needs_little_memory():
+    """One long, thin domain: cut into runs of a few planes it would be ten million records; the plan counts them
+    before it makes any."""
+    peak = fake_hip.run("""
+import resource
+b = make_batch("D3Q19", "f32", [(1, 1, 40_000_000)])
+lbm.lbm_batch_step(b, 2)
+assert all("k_batch_step" in l["name"] for l in fake.launches())
+out = resource.getrusage(resource.RUSAGE_SELF).ru_maxrss / 1024
+""")
+    assert peak < 300, peak  # MiB
+
+
+def test_schedule_there_and_back():
+    out = fake_hip.run("""
+out = []
+for lat, st, shape in (("D3Q19", "f64", (64, 64, 64)), ("D2Q9", "f32", (40, 30, 1))):
+    b = make_batch(lat, st, [shape] * 40)
+    names = []
+    for kw in ({}, dict(xcd_group=1), dict(), dict(mode="persistent", wg_per_cu=1, chunk_cells=4096), dict()):
+        lbm.lbm_batch_set_schedule(b, lbm.make_batch_schedule(**kw))
+        fake.launches()
+        lbm.lbm_batch_step(b, 6)
+        names.append([(l["name"], l["grid"], l["block"]) for l in fake.launches()])
+    out.append(names)
+""")
+    for first, xcd, again, persistent, last in out:
+        assert first == again == last and first != xcd
+        assert all("k_batch_step" in n for n, _, _ in xcd) and len(xcd) == 6
