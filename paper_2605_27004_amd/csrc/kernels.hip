@@ -1515,7 +1515,10 @@ hipError_t launch_moments(int lattice, int storage, const Grid &g, const StepCon
 }
 
 // Work-groups of whole rows, or of the widest part that long rows are a multiple of (384^3 FP16: 128 cells
-// 1,149 us, 256 1,434). Exports of rows of whole cache lines go past the caches (D3Q19 FP32 256^3 472 -> 437;
+// 1,149 us, 256 1,434). Without a mask that part is no better for imports of rows of 64 n cells, and worse
+// in D2Q9 (over 130 planes, 64-wide parts against 256: 1.26 of the time in 16-bit storage, up to 1.5; 1.16 FP32, 1.05
+// FP64; 128-wide parts 1.09 and 1.07; D3Q19 and D3Q27 1.01, 128-wide parts of 384 cells 0.87, of 640 cells 1.09), nor
+// for exports of D2Q9 to FP64 but from 16-bit storage of more than 80 MB (0.97; below 1.09). Exports of rows of whole cache lines go past the caches (D3Q19 FP32 256^3 472 -> 437;
 // D3Q27 FP32 150 x 101 x 75 the other way round, 47 against 64).
 hipError_t launch_permute(int lattice, int storage, int mode, const Grid &g, const StepConsts<double> &k,
                           const uint32_t *links, const void *src, void *dst, hipStream_t stream)
@@ -1526,7 +1529,11 @@ hipError_t launch_permute(int lattice, int storage, int mode, const Grid &g, con
             constexpr int LAT = decltype(lat)::value;
             const bool lines = g.nx * (int64_t)sizeof(S) % 128 == 0;
             dim3 block = row_block(g);
-            if (g.nx > 256 && g.nx % 64 == 0) {
+            const bool large = 2.0 * Lattice<LAT>::Q * sizeof(S) * g.n > 80e6;
+            const bool idle = 5 * g.nx < 4 * ((g.nx + 255) / 256 * 256);  // a fifth of 256-wide parts' lanes and more
+            const bool narrow = links || mode == 0 || (mode == 1 ? LAT != kD2Q9 && g.nx % 128 == 0 && idle
+                                                                : LAT != kD2Q9 || (sizeof(S) == 2 && large));
+            if (g.nx > 256 && g.nx % 64 == 0 && narrow) {
                 const int bx = g.nx % 256 == 0 ? 256 : (g.nx % 128 == 0 ? 128 : 64);
                 block = dim3((uint32_t)bx, (uint32_t)(256 / bx));
             }
