@@ -429,10 +429,14 @@ hipError_t mask_pays(const lbm_ctx *c, const uint8_t *mask, bool &compact)
     return hipSuccess;
 }
 
-// Most steps of one launch: a tiled launch's, the two of a sweep, or one.
-int64_t most_steps(const lbm_ctx *c) { return c->tile.shape >= 0 ? c->tile.steps : (c->sweep.tx ? 2 : 1); }
+// Most steps of one launch where n are to be taken: a tiled launch's, the two of a sweep, or one.
+int64_t most_steps(const lbm_ctx *c, int64_t n)
+{
+    if (c->tile.shape >= 0) return n >= c->tile.least ? c->tile.steps : 1;
+    return c->sweep.tx ? 2 : 1;
+}
 
-// One launch of k <= most_steps steps from src to dst.
+// One launch of k steps, at most most_steps, from src to dst.
 hipError_t launch_pass(const lbm_ctx *c, int64_t k, const void *src, void *dst)
 {
     if (k == 1)
@@ -448,7 +452,7 @@ hipError_t launch_pass(const lbm_ctx *c, int64_t k, const void *src, void *dst)
 // n >= 1 steps from src to dst through the context's population buffers (src may be neither of them).
 hipError_t advance(const lbm_ctx *c, const void *src, void *dst, int64_t n)
 {
-    int64_t left = launches_for(n, most_steps(c), c->stream);
+    int64_t left = launches_for(n, most_steps(c, n), c->stream);
     for (int i = 0; n > 0; i ^= 1, --left) {
         const int64_t k = steps_of_launch(n, left);
         void *out = k == n ? dst : c->pop[i];
@@ -463,7 +467,7 @@ hipError_t advance(const lbm_ctx *c, const void *src, void *dst, int64_t n)
 // n >= 0 steps from src, each state kept: state s (after s + 1 steps) at base + s stride bytes.
 hipError_t record(const lbm_ctx *c, const void *src, char *base, int64_t stride, int64_t n)
 {
-    for (int64_t left = launches_for(n, c->tile.shape >= 0 ? c->tile.steps : 1, c->stream); n > 0; --left) {
+    for (int64_t left = launches_for(n, c->tile.shape >= 0 ? most_steps(c, n) : 1, c->stream); n > 0; --left) {
         const int64_t k = steps_of_launch(n, left);
         const hipError_t e = k == 1 ? launch_pass(c, 1, src, base)
                                     : launch_tile(c->p.storage, c->p.order, c->grid, c->k64, c->k32, c->links, c->gray,
@@ -590,7 +594,7 @@ int lbm_init(lbm_ctx **out, const lbm_params *p, void *pop_a, void *pop_b, void 
     c->block_y = 256 / c->block_x;
     c->launch_flags = kLaunchDefault;
     c->sweep = SweepPlan{0, 0, 0};
-    c->tile = TilePlan{-1, 1};
+    c->tile = TilePlan{-1, 1, 1};
     const bool general = masked || grayed || c->k64.forced;
     if (p->lattice == LBM_D2Q9) {
         if (tile_serves(p->storage, grayed, masked || c->k64.forced))
@@ -635,7 +639,7 @@ int lbm_step(lbm_ctx *c, int64_t nsteps)
 {
     if (!c) return fail(LBM_ERR_ARG, "ctx is NULL");
     if (nsteps < 0) return fail(LBM_ERR_ARG, "nsteps must be >= 0");
-    for (int64_t left = launches_for(nsteps, most_steps(c), c->stream); nsteps > 0; --left) {
+    for (int64_t left = launches_for(nsteps, most_steps(c, nsteps), c->stream); nsteps > 0; --left) {
         const int64_t k = steps_of_launch(nsteps, left);
         const hipError_t e = launch_pass(c, k, c->pop[c->cur], c->pop[c->cur ^ 1]);
         if (e != hipSuccess) return fail_hip(e, "step kernel launch");
@@ -728,7 +732,7 @@ int lbm_set_launch(lbm_ctx *c, int32_t block_x, int32_t block_y, int32_t flags)
     c->block_y = block_y;
     c->launch_flags = flags;
     c->sweep = SweepPlan{0, 0, 0};  // the launch asked for is a single step's
-    c->tile = TilePlan{-1, 1};
+    c->tile = TilePlan{-1, 1, 1};
     return LBM_OK;
 }
 

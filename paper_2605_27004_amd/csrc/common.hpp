@@ -138,6 +138,7 @@ hipError_t launch_sweep(int lattice, int storage, int order, const Grid &g, cons
 // lattices, launches the caller has shaped, and grids on which single steps are the faster way).
 struct TilePlan {
     int shape, steps;
+    int least;  // steps from which on a call takes tiles
 };
 bool tile_serves(int storage, bool gray, bool links_or_force);
 TilePlan plan_tile(int storage, const Grid &g, bool general, bool gray);  // general: links, gray cells or a force

@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "cell.hpp"
 #include "common.hpp"
@@ -224,13 +225,24 @@ bool tile_serves(int storage, bool gray, bool links_or_force)
 TilePlan plan_tile(int storage, const Grid &g, bool general, bool gray)
 {
     const bool f64 = storage == kF64, f32 = storage == kF32;
+    const double cell_us = 1e-6 * g.n;
     TilePlan p;
-    if (g.n <= 8192) p = TilePlan{0, 8};
-    else if (g.n <= 100000) p = TilePlan{0, 6};
-    else if (g.n <= 400000) p = TilePlan{2, 6};
-    else if (f64) p = TilePlan{1, 4};
-    else if (f32) p = TilePlan{2, general ? 4 : 5};
-    else p = general ? TilePlan{1, 3} : TilePlan{2, 5};
+    if (g.n <= 8192) p = TilePlan{0, 8, 2};
+    else if (g.n <= 100000) p = TilePlan{0, 6, 2};
+    else if (g.n <= 400000) p = TilePlan{2, 6, 2};
+    else if (f64) p = TilePlan{1, 4, 2};
+    else if (f32) p = TilePlan{2, general ? 4 : 5, 2};
+    else p = general ? TilePlan{1, 3, 2} : TilePlan{2, 5, 2};
+    if (p.shape == 2) {
+        // a launch of the large tile takes 8 to 12 us whatever its steps, so two steps alone may lose (us per step,
+        // single against tile: FP32 400 x 300 3.6 / 4.3, with a force 3.8 / 4.8, 512^2 5.9 / 4.6; BF16 512^2 4.0 / 5.0,
+        // 1000 x 700 7.4 / 6.4; FP64 400 x 300 with a force 5.0 / 6.4, 576 x 664 12.3 / 7.8)
+        const double t2 = (double)((g.nx + 61) / 62) * (double)((g.ny + 29) / 30);
+        const double two_us = f64   ? (general ? 11.3 : 9.0) + 0.02 * t2
+                              : f32 ? (general ? 8.2 : 7.5) + 0.015 * t2 + (t2 > 256.0 ? 4.0 : 0.0)
+                                    : (general ? 9.6 + 0.017 * t2 : 8.2 + 0.0125 * t2);
+        if (two_us >= 2.0 * std::max(3.7, 2.8 + (f64 ? 20.0 : (f32 ? 10.0 : (general ? 7.3 : 5.8))) * cell_us)) p.least = 3;
+    }
 
     const TileShape &sh = kShapes[p.shape];
     const int ow = sh.tw - 2 * (p.steps - 1), oh = sh.height() - 2 * (p.steps - 1);
@@ -239,15 +251,17 @@ TilePlan plan_tile(int storage, const Grid &g, bool general, bool gray)
                            : f32 ? (gray ? 1.1 : (general ? 1.4 : 0.85))
                                  : (gray ? 1.25 : (general ? 1.35 : 0.78));
     const double turn_us = 1e-3 * cell_ns * p.steps * sh.tw * (sh.height() - p.steps + 1);
-    const double launch_us = p.shape == 2 ? 5.0 + turn_us * std::max(1.0, turns + 0.75)
+    // (with links or a force in 16-bit storage the large tile's registers leave room for one: whole turns count)
+    const double large_turns = !f64 && !f32 && general && !gray ? std::ceil(turns) : std::max(1.0, turns + 0.75);
+    const double launch_us = p.shape == 2 ? 5.0 + turn_us * large_turns
                                           : (p.shape == 0 ? 6.5 : 9.0) + turn_us * turns;
     // (past the Infinity Cache a quarter more in FP64, a fifth in FP32)
     const bool large = 18.0 * (f64 ? 8 : (f32 ? 4 : 2)) * g.n > 300e6;
     const double cell_ps = f64 ? (large ? 25.0 : 20.0) : (f32 ? (large ? 12.0 : 10.0) : (general ? 7.3 : 5.8));
     // (rows that the lane exchange serves are at the model's lower side, others at its upper side)
     const double factor = g.nx % 64 == 0 && g.nx <= 256 ? (f64 || f32 ? 1.0 : 0.95) : 1.1;
-    const double single_us = std::max(3.9, factor * (2.8 + 1e-6 * cell_ps * g.n));
-    return launch_us / p.steps < single_us ? p : TilePlan{-1, 1};
+    const double single_us = std::max(3.9, factor * (2.8 + cell_ps * cell_us));
+    return launch_us / p.steps < single_us ? p : TilePlan{-1, 1, 1};
 }
 
 hipError_t launch_tile(int storage, int order, const Grid &g, const StepConsts<double> &k64,

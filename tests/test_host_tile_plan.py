@@ -38,3 +38,19 @@ def test_planes_take_tiles(walls):
              if not (st == "f16" and ("force" in walls or "masked" in walls))]
     for g, route in zip(grids, _routes(grids)):
         assert route == ["k_tile"], g
+
+
+def test_two_steps_over_a_middling_plane_are_single_steps():
+    out = fake_hip.run("""
+out = []
+for st, nx, ny in (("f32", 400, 300), ("bf16", 512, 512), ("f32", 512, 512), ("f64", 64, 64), ("f64", 576, 664)):
+    c = make("D2Q9", st, (nx, ny, 1))
+    row = []
+    for n in (2, 3):
+        lbm.lbm_step(c, n)
+        row.append(["k_tile" in l["name"] for l in fake.launches()])
+    out.append(row)
+    lbm.lbm_destroy(c)
+""")
+    single, tiled = [[False, False], [True]], [[True], [True]]
+    assert out == [single, single, tiled, tiled, tiled]
