@@ -163,7 +163,7 @@ int64_t lbm_scratch_bytes(const lbm_params *p);
  *                 call's device work only.
  *   stream:       hipStream_t for all work of this context.
  * On success *out receives the context (free with lbm_destroy). Asynchronous, but for masked
- * three-dimensional grids in FP64 or FP32 with nx a multiple of 64 and 64 MB of populations or more: what
+ * three-dimensional grids in FP64 (20 MB of populations or more) or FP32 (64 MB) with nx a multiple of 64: what
  * suits the mask decides how their rows are stored, and the call waits for the stream to learn it
  * (not while the stream is being recorded into a graph). */
 int lbm_init(lbm_ctx **out, const lbm_params *p, void *pop_a, void *pop_b, void *scratch, const double *rho0,

@@ -365,14 +365,15 @@ template <typename C> StepConsts<C> consts_for(const lbm_params &p, const Prepar
 
 // Whether a masked grid may store its rows compact (RowRec); whether it does, the mask decides (compact_pays).
 // The index fits in the link words' share of the scratch: 8 ceil(nx / 30) + 4 + 2 nx bytes for a row, against
-// 4 nx. Not below 64 MB of populations and, in FP32, not on rows of 64 cells: the row index, read before
-// anything else can start, costs more than it gives there (D3Q19 FP64 64 x 24 x 24 1.05 to 1.13 of the time
-// over all masks, FP32 64^3 10.0 -> 10.4 us). Never for 16-bit storage, where the lookups cost as much as the solid
+// 4 nx. Not below 20 MB of populations in FP64, and not below 64 MB nor on rows of 64 cells in FP32: the row index,
+// read before anything else can start, costs more than it gives there (D3Q19 FP64 64 x 24 x 24 and 64 x 30 x 28 1.05
+// to 1.2 of the time over all masks, FP32 64^3 10.0 -> 10.4 us). Never for 16-bit storage, where the lookups cost as much as the solid
 // cells' bytes (D3Q27 FP16 256^3 319 -> 304 and 324 -> 329 us, but 384 -> 471 with 10% random single cells).
 bool compact_rows(const lbm_params &p, int q, int bytes, uint32_t n)
 {
     if (p.lattice == LBM_D2Q9 || p.nx % 64 != 0 || p.nx > (int64_t)kMaxCompactRow) return false;
-    return 2.0 * q * bytes * n >= 64e6 && (bytes == 8 || (bytes == 4 && p.nx >= 128));
+    const double both = 2.0 * q * bytes * n;
+    return bytes == 8 ? both >= 20e6 : (bytes == 4 && p.nx >= 128 && both >= 64e6);
 }
 
 // Whether compact rows are the faster way for a mask: `solid` of the n cells, in `runs` runs along x. What
@@ -381,10 +382,11 @@ bool compact_rows(const lbm_params &p, int q, int bytes, uint32_t n)
 // 53.2 -> 54.5, 5% (10%) of random cells 55.8 -> 61.0 (56.6 -> 62.5), 21% in ellipsoids 0.98 of the time, 40%
 // 53.4 -> 45.6, 22% (30%) random 1.04 (57.5 -> 52.9); 256^3 22% outside a pipe 0.89, 20% in ellipsoids 0.90, 40%
 // 416 -> 309, 10% (22%) random 454 -> 473 (456 -> 430); D3Q27 256^3 40% 590 -> 443; FP64 D3Q19 128^3 none 108 -> 107, 12% random 0.92 to 0.98,
-// 40% in ellipsoids 102 -> 80; 64^3 12% random 1.07, 30% random 0.88, 31% in ellipsoids 0.99.
+// 40% in ellipsoids 102 -> 80; 64^3 12% random 1.07, 30% random 0.88, 31% in ellipsoids 0.99; 20 to 60 MB (13 grids)
+// 30% in ellipsoids 0.75 to 1.07, 40% 0.74 to 1.09, 20% 0.76 to 1.2.
 bool compact_pays(int bytes, double both, double n, double solid, double runs)
 {
-    const double least = bytes == 8 ? (both >= 200e6 ? 0.07 : 0.2) : (both >= 500e6 ? 0.14 : 0.2);
+    const double least = bytes == 8 ? (both >= 200e6 ? 0.07 : (both >= 64e6 ? 0.2 : 0.28)) : (both >= 500e6 ? 0.14 : 0.2);
     return (solid - 0.4 * runs) / n >= least;
 }
 

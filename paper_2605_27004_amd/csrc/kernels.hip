@@ -1351,10 +1351,10 @@ struct StepShape {
 // named otherwise:
 //  * Rows that are a multiple of 64 cells, up to 256 (and not the links step): the lane exchange.
 //    Its stores are whole cache lines; they stay in the caches where both population arrays come
-//    near the 256 MB Infinity Cache (80 to 400 MB: FP32 gray 128^3 52.8 -> 49.2, 192 x 128 x 100
-//    63.9 -> 58.0, FP16 128^3 27.6 -> 26.7), and go past them where the grid is larger (192^3 FP32
-//    gray 178.5 against 198.9 cached, FP64 gray 128^3 102.7 against 111.1) or smaller (64^3 FP32
-//    7.1 against 8.1).
+//    near the 256 MB Infinity Cache (80 to 400 MB, in FP64 from 90 MB on: FP32 gray 128^3 52.8 -> 49.2,
+//    192 x 128 x 100 63.9 -> 58.0, FP16 128^3 27.6 -> 26.7), and go past them where the grid is larger (192^3
+//    FP32 gray 178.5 against 198.9 cached, FP64 gray 128^3 102.7 against 111.1) or smaller (64^3 FP32 7.1
+//    against 8.1, D3Q27 FP64 64 x 64 x 46 15.5 against 17.6).
 //  * Other row lengths leave lanes of a box idle and, where a row is no whole number of cache
 //    lines, parts of lines at both ends of every row: work-groups then take 256 consecutive
 //    cells whatever rows they lie in, and cached stores, 16 neighbouring tiles on one XCD, let
@@ -1388,7 +1388,7 @@ StepShape step_shape(int mode, int lat, size_t bytes, const Grid &g, int block_x
     const uint32_t group = mode == kLinks ? 0u : (bytes == 2 && !shaped ? 4u : 1u);
     const double q = lat == kD2Q9 ? 9 : (lat == kD3Q19 ? 19 : 27);
     const double both = 2.0 * q * (double)bytes * g.n;
-    const bool near = both >= 80e6 && both <= 400e6;
+    const bool near = both >= (bytes == 8 ? 90e6 : 80e6) && both <= 400e6;
     if (!shaped && g.nx % 64 != 0) {
         const size_t row = (size_t)g.nx * bytes;
         const bool l2 = bytes < 8 && both >= 12e6 && both <= 20e6;
@@ -1517,7 +1517,7 @@ hipError_t launch_moments(int lattice, int storage, const Grid &g, const StepCon
 // Work-groups of whole rows, or of the widest part that long rows are a multiple of (384^3 FP16: 128 cells
 // 1,149 us, 256 1,434). Without a mask that part is no better for imports of rows of 64 n cells, and worse
 // in D2Q9 (over 130 planes, 64-wide parts against 256: 1.26 of the time in 16-bit storage, up to 1.5; 1.16 FP32, 1.05
-// FP64; 128-wide parts 1.09 and 1.07; D3Q19 and D3Q27 1.01, 128-wide parts of 384 cells 0.87, of 640 cells 1.09), nor
+// FP64; 128-wide parts 1.09 and 1.07; D3Q19 and D3Q27 64-wide parts of 320 cells 0.76, 128-wide ones of 384 cells 0.87, of 640 cells 1.09), nor
 // for exports of D2Q9 to FP64 but from 16-bit storage of more than 80 MB (0.97; below 1.09). Exports of rows of whole cache lines go past the caches (D3Q19 FP32 256^3 472 -> 437;
 // D3Q27 FP32 150 x 101 x 75 the other way round, 47 against 64).
 hipError_t launch_permute(int lattice, int storage, int mode, const Grid &g, const StepConsts<double> &k,
@@ -1531,7 +1531,7 @@ hipError_t launch_permute(int lattice, int storage, int mode, const Grid &g, con
             dim3 block = row_block(g);
             const bool large = 2.0 * Lattice<LAT>::Q * sizeof(S) * g.n > 80e6;
             const bool idle = 5 * g.nx < 4 * ((g.nx + 255) / 256 * 256);  // a fifth of 256-wide parts' lanes and more
-            const bool narrow = links || mode == 0 || (mode == 1 ? LAT != kD2Q9 && g.nx % 128 == 0 && idle
+            const bool narrow = links || mode == 0 || (mode == 1 ? LAT != kD2Q9 && idle
                                                                 : LAT != kD2Q9 || (sizeof(S) == 2 && large));
             if (g.nx > 256 && g.nx % 64 == 0 && narrow) {
                 const int bx = g.nx % 256 == 0 ? 256 : (g.nx % 128 == 0 ? 128 : 64);

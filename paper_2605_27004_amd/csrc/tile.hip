@@ -241,15 +241,19 @@ TilePlan plan_tile(int storage, const Grid &g, bool general, bool gray)
         const double two_us = f64   ? (general ? 11.3 : 9.0) + 0.02 * t2
                               : f32 ? (general ? 8.2 : 7.5) + 0.015 * t2 + (t2 > 256.0 ? 4.0 : 0.0)
                                     : (general ? 9.6 + 0.017 * t2 : 8.2 + 0.0125 * t2);
-        if (two_us >= 2.0 * std::max(3.7, 2.8 + (f64 ? 20.0 : (f32 ? 10.0 : (general ? 7.3 : 5.8))) * cell_us)) p.least = 3;
+        // (long rows of 64 n cells have slower single steps: boxes)
+        const double ps = (f64 ? 20.0 : (f32 ? (general ? 11.0 : 10.0) : (general ? 7.3 : 5.8))) *
+                          (g.nx > 256 && g.nx % 64 == 0 ? 1.2 : 1.0);
+        if (two_us >= 2.0 * std::max(3.7, 2.8 + ps * cell_us)) p.least = 3;
     }
+    if (p.steps == 3 && g.n < 1000000) p.least = 3;  // (BF16 448 x 1017 with a force 6.1 / 7.4)
 
     const TileShape &sh = kShapes[p.shape];
     const int ow = sh.tw - 2 * (p.steps - 1), oh = sh.height() - 2 * (p.steps - 1);
     const double tiles = (double)((g.nx + ow - 1) / ow) * (double)((g.ny + oh - 1) / oh), turns = tiles / 256.0;
     const double cell_ns = f64   ? (gray ? 1.8 : (general ? 1.9 : 1.27))
                            : f32 ? (gray ? 1.1 : (general ? 1.4 : 0.85))
-                                 : (gray ? 1.25 : (general ? 1.35 : 0.78));
+                                 : (gray ? 1.25 : (general ? (p.shape == 2 ? 1.6 : 1.35) : 0.78));
     const double turn_us = 1e-3 * cell_ns * p.steps * sh.tw * (sh.height() - p.steps + 1);
     // (with links or a force in 16-bit storage the large tile's registers leave room for one: whole turns count)
     const double large_turns = !f64 && !f32 && general && !gray ? std::ceil(turns) : std::max(1.0, turns + 0.75);

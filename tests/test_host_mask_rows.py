@@ -30,7 +30,8 @@ def test_the_mask_decides():
              ("D3Q27", "f32", wide, 0.30, 0.21, False, True, True), ("D3Q27", "f32", large, 0.22, 0.0, False, True, True),
              ("D3Q19", "f64", large, 0.016, 0.0, False, False, True), ("D3Q19", "f64", large, 0.12, 0.01, False, True, True),
              ("D3Q19", "f64", large, 0.05, 0.047, False, False, True), ("D3Q27", "f64", small, 0.17, 0.14, False, False, True),
-             ("D3Q27", "f64", small, 0.30, 0.21, False, True, True), ("D3Q19", "f64", (64, 24, 24), 0.6, 0.03, False, False, False),
+             ("D3Q27", "f64", small, 0.30, 0.21, False, True, True), ("D3Q19", "f64", (128, 28, 28), 0.40, 0.02, False, True, True),
+             ("D3Q19", "f64", (128, 28, 28), 0.22, 0.01, False, False, True), ("D3Q19", "f64", (64, 24, 24), 0.6, 0.03, False, False, False),
              ("D3Q19", "f32", small, 0.6, 0.03, False, False, False), ("D3Q27", "f16", large, 0.6, 0.03, False, False, False),
              # a stream that is being recorded cannot be waited for
              ("D3Q19", "f32", large, 0.40, 0.023, True, False, False)]
