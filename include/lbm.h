@@ -26,7 +26,10 @@
  *    The canonical state at integer t is the PRE-collision f_i(t, x) of eq:LBE_BGK; every
  *    read-out call refers to it, whatever the library keeps internally.
  *  - Device pointers are HIP device addresses owned by the caller; they must stay valid
- *    for the lifetime of the context. The library allocates no device memory.
+ *    for the lifetime of the context. The library allocates no device memory. Calls that return
+ *    totals or an objective (lbm_moments, lbm_objective, lbm_grad, lbm_batch_moments), and lbm_init
+ *    where it reads numbers of a mask, take them through pinned host memory: one block of 512 KiB
+ *    for the process, allocated at the first such call and kept.
  *  - Every call returns LBM_OK (0) or a negative LBM_ERR_* code; no exception crosses the
  *    ABI. lbm_last_error() returns a thread-local message for the last failing call.
  *    Parameter errors are detected on the host before any device work is enqueued.
@@ -144,7 +147,8 @@ int64_t lbm_pop_bytes(const lbm_params *p);
 /* Rows per block of the private population layout (host only): each z-plane is stored as
  * ny / rows blocks of `rows` consecutive y-rows, a block holding its q direction planes one
  * after another; rows is the largest divisor of ny with rows * nx * sizeof(storage) <= 8 KiB
- * (32 KiB for FP64), at least 1. For tests and tools; -1 if p is invalid. */
+ * (32 KiB for FP64), at least 1. Within a row the cells lie in the order of x; masked grids may store a
+ * row's fluid cells first instead (see lbm_init). For tests and tools; -1 if p is invalid. */
 int64_t lbm_rows_per_block(const lbm_params *p);
 
 /* Bytes of device scratch lbm_init needs (reduction partials, plus 4 bytes per cell for what the
@@ -220,7 +224,8 @@ int64_t lbm_time(const lbm_ctx *ctx);
  * 64, block_x * block_y <= 256) and flags. The default spans whole x rows up to 256 cells
  * (block_y = 256 / block_x rows); longer rows take the width of 256, 128 or 64 cells that pads
  * the row least, the widest on a tie; rows that are no multiple of 64 cells take 256 consecutive
- * cells of a z-plane. A launch set here makes one step each. */
+ * cells of a z-plane. By default, the single steps of a grid that otherwise makes two in a launch take
+ * LBM_LAUNCH_XCD_SLABS if both its buffers hold less than 100 MB. A launch set here makes one step each. */
 #define LBM_LAUNCH_XCD_SLABS 1    /* hand each of the 8 XCDs one contiguous slab of tiles */
 #define LBM_LAUNCH_SHIFTED_PULL 2 /* pull every population with its own shifted load. By default, when
                                      nx is a multiple of 64 and block_x == nx (work-groups of whole
@@ -342,7 +347,8 @@ int64_t lbm_batch_scratch_bytes(const lbm_batch_params *p);
  *   pop_a, pop_b: device, lbm_batch_pop_bytes each, 256-byte aligned.
  *   scratch:      device, lbm_batch_scratch_bytes, 256-byte aligned.
  *   rho0, s0:     device FP64 [C] and [d][C], read during the call.
- * Synchronises the stream before returning. Starts with the step-per-launch schedule. */
+ * Synchronises the stream before returning. Starts with the stepwise schedule in domain-major order
+ * (LBM_BATCH_STEPWISE, xcd_group 0). */
 int lbm_batch_init(lbm_batch **out, const lbm_batch_params *p, void *pop_a, void *pop_b, void *scratch,
                    const double *rho0, const double *s0, void *hip_stream);
 

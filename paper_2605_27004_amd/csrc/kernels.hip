@@ -78,6 +78,13 @@ __device__ inline uint32_t tile_of(const TileMap &m, uint32_t b)
 // aid that moves exactly the step's bytes in the step's pattern.
 enum StepMode : int { kPlain = 0, kLinks = 1, kGray = 2, kStream = 3 };
 
+// How the step kernel pulls (launch_step picks): every population with its own shifted load, in
+// work-groups that are boxes of block_x x block_y cells (kPullShifted) or runs of 256 consecutive
+// cells of a z-plane (kPullFlat); or the lane exchange inside whole rows (kPullRows: pull_aligned, or
+// pull_rows_lds for FP16 storage). kPullCompact: the links step over compact rows
+// (RowRec), where x counts a row's fluid cells; kPullCompactWide: the same for populations of 4 GiB and more.
+enum PullKind : int { kPullShifted = 0, kPullRows = 1, kPullFlat = 2, kPullCompact = 3, kPullCompactWide = 4 };
+
 // Pull of a cell's q pre-collision deviations when every work-group spans whole grid rows: nx
 // is a multiple of 64 and the work-group is nx wide (launch_step checks this). An x-shifted pull
 // would make each wave read three cache lines of which two are shared with the neighbouring
@@ -90,13 +97,6 @@ enum StepMode : int { kPlain = 0, kLinks = 1, kGray = 2, kStream = 3 };
 // edge values would need loads of their own; measured that way, the exchange lost to shifted
 // loads (D3Q19 FP32 512^3: 3.55 vs 3.40 ms per step; 448^3 in 64-wide work-groups: 2.83 vs
 // 2.24 ms), so such launches use the shifted pull.
-// How the step kernel pulls (launch_step picks): every population with its own shifted load, in
-// work-groups that are boxes of block_x x block_y cells (kPullShifted) or runs of 256 consecutive
-// cells of a z-plane (kPullFlat); or the lane exchange inside whole rows (kPullRows: pull_aligned, or
-// pull_rows_lds for FP16 storage). kPullCompact: the links step over compact rows
-// (RowRec), where x counts a row's fluid cells; kPullCompactWide: the same for populations of 4 GiB and more.
-enum PullKind : int { kPullShifted = 0, kPullRows = 1, kPullFlat = 2, kPullCompact = 3, kPullCompactWide = 4 };
-
 template <int LAT, typename S, int PULL>
 __device__ inline void pull_aligned(const S *__restrict__ src, const Grid &g, const Cell &c, int32_t x, bool live,
                                     typename Conv<S>::C *gp, typename Conv<S>::C *gm)

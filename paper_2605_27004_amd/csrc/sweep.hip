@@ -10,11 +10,11 @@
 // in between, so the result is bit for bit that of two single steps.
 //
 // What bounds it: the first step is made again on the tile's rim (11 rows of lanes for 8 rows of
-// cells at the D3Q19 256^3 tile below), so FP32 is bound by its VALU work (596 instructions per
-// two steps and cell, VALU 78% busy, the clock down to 1.7 GHz) and FP64 by HBM and LDS space (one
-// work-group of 10 waves per compute unit). Us per step, two single steps -> sweep:
-//   D3Q19 FP32 256^3 389.6 -> 262.5, 128^3 52.1 -> 38.4; FP64 256^3 808.9 -> 505.0,
-//   250 x 190 x 130 404.6 -> 193.1; D3Q27 FP32 256^3 564.8 -> 447.4, FP64 256^3 1191 -> 904.
+// cells at the D3Q19 256^3 tile below), so FP32 is bound by its VALU work (753 instructions per
+// two steps and cell, VALU 70% busy, the clock down to 1.95 GHz) and FP64 by HBM and LDS space (one
+// work-group of 10 waves per compute unit; 5.4 TB/s, VALU 30% busy). Us per step, two single steps ->
+// sweep: D3Q19 FP32 256^3 387.6 -> 262.7, 128^3 48.3 -> 37.0; FP64 256^3 801.7 -> 508.5,
+//   250 x 190 x 130 356.2 -> 190.2; D3Q27 FP32 256^3 556.0 -> 428.6, FP64 256^3 1175 -> 898.
 //
 //  * Lanes: wave w of the tile is one row of 64 cells (two of 32), so the stores of a wave are
 //    whole cache lines, and the columns left and right of the tile sit in the last waves. One flat

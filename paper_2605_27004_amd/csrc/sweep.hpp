@@ -1,4 +1,4 @@
-// sweep.hpp -- the plane loop of the two-step sweeps (sweep.hip: one grid; batch.hip: a batch of
+// sweep.hpp -- the plane loop of the two-step sweeps (sweep.hip: one grid; batch_sweep.hip: a batch of
 // domains): two steps of the periodic update on a tile of columns, walking up in z. What bounds it and
 // why it is built so stands in sweep.hip.
 #pragma once

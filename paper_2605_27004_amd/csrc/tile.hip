@@ -11,9 +11,9 @@
 // rounded to the storage type in between), so the result is bit for bit the single steps'.
 //
 // What bounds it then: large grids the VALU work (rim included 1.2 x the single steps'), small ones
-// the latency of a step in LDS (0.65 us). Us per step, single -> tiles: 64^2 FP64 3.65 -> 1.0, 512^2
-// FP32 with gray cells 6.4 -> 3.3, 1000 x 700 FP64 20.0 -> 8.4, 3000 x 2000 FP32 83.5 -> 33.0,
-// 4096^2 FP32 193.6 -> 90.6, 2816 x 2746 FP16 55.9 -> 35.5.
+// the latency of a step in LDS (0.65 us). Us per step, single -> tiles: 64^2 FP64 3.9 -> 1.0, 512^2
+// FP32 with gray cells 6.2 -> 3.5, 1000 x 700 FP64 16.5 -> 8.3, 3000 x 2000 FP32 76.5 -> 33.2,
+// 4096^2 FP32 193.7 -> 90.0, 2816 x 2746 FP16 46.6 -> 34.2.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
